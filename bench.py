@@ -162,6 +162,7 @@ def streaming_line(gwd, blobs, x, out, ref_scores, args):
     Wl = 1 << 20
     Sl = Wl - 3072
     m = gwd.Model(gwd.full_arch(), blobs, args.precision)
+    m.set_window_merging(False)   # every row of every window is computed
     L = x.shape[0]
 
     def step(xx=x):
@@ -218,6 +219,7 @@ def ragged_workload(gwd, blobs, prec: str):
                 x[lo:hi] += torch.from_numpy(synth.injection_signal(inj, lo / FS, hi - lo).astype(np.float32)).cuda()
         bufs.append(x)
     m = gwd.Model(gwd.full_arch(), blobs, prec)
+    m.set_window_merging(False)   # every row of every window is computed
     rows, waves, fuse, batch, blocks, persistent = m.autotune([bufs[0][: 64 * FS]])
     offs = np.concatenate([[0], np.cumsum(lens)])
     total_s = sum(lens) / FS
@@ -270,6 +272,7 @@ def background_workload(gwd, blobs, x, prec: str, seconds: float = 900.0, n_slid
     L = xs.shape[0]
     shifts = [k * int(step_s * FS) for k in range(1, n_slides + 1)]
     m = gwd.Model(gwd.full_arch(), blobs, prec)
+    m.set_window_merging(False)   # every row of every window is computed
     warm = gwd.time_slide(xs[: 64 * FS], shifts)
     m.forward([warm[k] for k in range(n_slides)], W, S, out_mode=0)
     del warm
@@ -336,6 +339,7 @@ def two_branch_workload(gwd, x, prec: str, seconds: float = 256.0, members: int 
     L = xs.shape[0]
     blobs = np.stack([synth.two_branch_weights(21 + i) for i in range(members)])
     m = gwd.Model(gwd.two_branch_arch(), blobs, prec)
+    m.set_window_merging(False)   # every row of every window is computed
     out = torch.empty(L, dtype=torch.float32, device="cuda")
     m.forward([xs[: 64 * FS]], W, S, out_mode=0, out=out)
     torch.cuda.synchronize()
@@ -537,6 +541,7 @@ def main():
     def run(prec, seconds=None):
         xs = x if seconds is None else x[: int(round(seconds * FS))]
         m = gwd.Model(gwd.full_arch(), blobs, prec)
+        m.set_window_merging(False)   # every row of every window is computed
         n_trig = [0]
 
         def step(xx=xs):

@@ -466,6 +466,18 @@ gwd_status gwd_set_fused_blocks(gwd_model* model, int32_t blocks);
  * GWD_ERR_UNSUPPORTED for other models (FP32, small member, two-branch). */
 gwd_status gwd_set_persistent(gwd_model* model, int32_t on);
 
+/* Overlapping windows of a stitched forward (out_mode 0 or 1; gated models; on = 1, the default).
+ * A stitched score depends on its stream alone, since window - stride >=
+ * receptive field - 1, so gwd_forward and plans created afterwards run each
+ * stream as one window, or as windows that overlap by the receptive field
+ * only, and compute no row twice that the scores do not need twice. The
+ * scores are bit for bit those of the request's own windows, and the
+ * workspace is no larger. on = 0 runs every row of every window of the request, as an engine that maps
+ * windows to windows does ("Optimization with TensorRT"). out_mode 2, the
+ * small member and the persistent forward always do. GWD_ERR_ARG unless on is
+ * 0 or 1. */
+gwd_status gwd_set_window_merging(gwd_model* model, int32_t on);
+
 /* Autotuner (the engine's kernel choice by profiling, "Optimization with
  * TensorRT"): times gwd_forward (out_mode 0) on the given request for every
  * schedule candidate (BF16/FP8: fused launches aiming at 512, 1024 and 2048

@@ -175,6 +175,42 @@ gwd_status check_forward(const gwd_model* m, const gwd_stream* streams, int32_t 
     return GWD_OK;
 }
 
+// The windows a stitched forward (out_mode 0 or 1) of a gated member runs. Every sample is scored by one
+// row of one window, and since window - stride >= RF - 1 that row's receptive field lies inside the
+// window or before the stream (zero context in both): the score depends on the stream alone, and every
+// row goes through the same operations wherever it sits in a window. Windows of 4096 at stride 256
+// compute each row 16 times over; here each stream becomes one window, or windows that overlap by the
+// receptive field only. A single stream is split evenly into windows of at most one batch of rows
+// (batch_windows x window, so the workspace is never larger than the request's own windows need);
+// several streams share a batch, with windows of at most an eighth of it, and each window stops at its
+// stream's end (FwdBatch::rows). Scores are bit for bit those of the request's own windows. Windows
+// 4096 / 256, four members in BF16: 8 s of strain 15.1 -> 1.94 ms, 256 s 459 -> 31.3 ms; one FP32
+// member, 16 s: 84.6 -> 6.03 ms.
+static bool merged_windows(const gwd_model* m, const gwd_stream* streams, int n_streams, int64_t total_win, int& window,
+                           int& stride) {
+    const int64_t H = (rf_of(&m->arch) - 1 + 127) / 128 * 128;   // overlap: whole 128-row tiles
+    int64_t longest = 0;
+    for (int s = 0; s < n_streams; ++s) longest = std::max<int64_t>(longest, streams[s].length);
+    const int64_t batch = std::min<int64_t>((int64_t)m->batch_windows * window, 1 << 22);
+    const int64_t cap = std::max<int64_t>(window, (n_streams == 1 ? batch : batch / 8) / 128 * 128);
+    int64_t W = (longest + 127) / 128 * 128, S = W;
+    if (W > cap) {
+        if (cap <= H) return false;
+        const int64_t n = (longest - H + cap - H - 1) / (cap - H);
+        S = ((longest - H + n - 1) / n + 127) / 128 * 128;
+        W = S + H;
+    }
+    int64_t rows = 0;
+    for (int s = 0; s < n_streams; ++s) {
+        const int64_t n = nwin_of(streams[s].length, (int)W, (int)S);
+        rows += streams[s].length + (n > 1 ? (n - 1) * (W - S) : 0);
+    }
+    if (rows >= total_win * window) return false;
+    window = (int)W;
+    stride = (int)S;
+    return true;
+}
+
 gwd_status ensure_workspace(gwd_model* m, int64_t bytes, hipStream_t st) {
     if (m->ws.bytes >= bytes) return GWD_OK;
     hipError_t e;
@@ -210,15 +246,26 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
         set_error("gwd_forward: FP64 models serve the training gradient checks only");
         return GWD_ERR_UNSUPPORTED;
     }
-    if (nwin_out) *nwin_out = nwin;
     nb_max = 0;
-    if (total_win == 0) return GWD_OK;
+    if (total_win == 0) {
+        if (nwin_out) *nwin_out = nwin;
+        return GWD_OK;
+    }
     const bool persist = m->persistent;
     if (persist && !persistent_supported(m, window)) {
         set_error("gwd_forward: the persistent forward needs every layer in a fused launch (a gated BF16/FP8 model, "
                   "a fused schedule, windows up to 4096); window %d", window);
         return GWD_ERR_UNSUPPORTED;
     }
+    // rows in a batch of the request's own windows; the merged ones stay within it
+    const int64_t batch_rows = (int64_t)m->batch_windows * window;
+    const bool merged = m->merge_windows && !persist && m->arch.kind == 1 && out_mode != 2 &&
+                        merged_windows(m, streams, n_streams, total_win, window, stride);
+    if (merged) {
+        total_win = 0;
+        for (int i = 0; i < n_streams; ++i) total_win += nwin[i] = nwin_of(streams[i].length, window, stride);
+    }
+    if (nwin_out) *nwin_out = nwin;
     hipError_t e = hipSetDevice(m->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     // device table: one StreamDesc per stream, then the global index of every stream's first window
@@ -239,7 +286,13 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
         wb += nwin[i];
         sb += streams[i].length;
     }
-    nb_max = (int)std::min<int64_t>(m->batch_windows, total_win);
+    std::vector<int32_t>& rows = m->host_rows;
+    rows.clear();
+    if (merged)
+        for (int i = 0; i < n_streams; ++i)
+            for (int64_t k = 0; k < nwin[i]; ++k)
+                rows.push_back((int32_t)std::min<int64_t>(window, streams[i].length - k * stride));
+    nb_max = (int)std::min<int64_t>(merged ? std::max<int64_t>(1, batch_rows / window) : m->batch_windows, total_win);
     if (m->arch.kind == 1) {
         // long windows: cap the windows per batch so the activations (x ping-pong and skip, 3 x 512 B
         // per time step) stay within 60 % of the device memory free now (plus what the model holds)
@@ -256,7 +309,8 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
     // tables), then x ping-pong and skip (persistent: the blocks' own buffers)
     const int64_t desc_bytes = (int64_t)n_streams * (int64_t)sizeof(StreamDesc);
     const int64_t first_bytes = (int64_t)firsts.size() * (int64_t)sizeof(int64_t);
-    const int64_t stream_bytes = (desc_bytes + first_bytes + 255) & ~255LL;
+    const int64_t row_bytes = (int64_t)rows.size() * (int64_t)sizeof(int32_t);
+    const int64_t stream_bytes = (desc_bytes + first_bytes + row_bytes + 255) & ~255LL;
     const int64_t persist_bytes = persist ? persistent_table_bytes(m, window) : 0;
     const int64_t tab_bytes = std::max<int64_t>(m->ws_tab_bytes, stream_bytes + persist_bytes);
     int64_t act_bytes = m->arch.kind == 1 ? 3 * (int64_t)nb_max * window * kC * 4 : 0;
@@ -273,9 +327,10 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
     s = ensure_workspace(m, tab_bytes + act_bytes, st);
     if (s != GWD_OK) return s;
     m->ws_tab_bytes = tab_bytes;
-    std::vector<char> host_tab(persist ? stream_bytes + persist_bytes : desc_bytes + first_bytes);
+    std::vector<char> host_tab(persist ? stream_bytes + persist_bytes : desc_bytes + first_bytes + row_bytes);
     memcpy(host_tab.data(), tab.data(), desc_bytes);
     memcpy(host_tab.data() + desc_bytes, firsts.data(), first_bytes);
+    if (row_bytes) memcpy(host_tab.data() + desc_bytes + first_bytes, rows.data(), row_bytes);
     StreamDesc* d_tab = (StreamDesc*)m->ws.base;
     if (persist) {  // the launch tables point at the stream table and the request's output
         FwdBatch pf{};
@@ -304,6 +359,8 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
     m->last_T = window;
     fb.streams = d_tab;
     fb.firsts = (const int64_t*)((const char*)d_tab + desc_bytes);
+    fb.rows = merged ? (const int32_t*)((const char*)d_tab + desc_bytes + first_bytes) : nullptr;
+    fb.h_rows = merged ? rows.data() : nullptr;
     fb.n_streams = n_streams;
     fb.T = window;
     fb.S = stride;

@@ -61,6 +61,7 @@ struct LayerArgsF32 {
     const float4* wrs;
     const float* brs;
     int d, T, tiles_per_window;
+    const int32_t* win_rows;  // per window: rows anyone needs (null: all T)
     // input projection straight from the strain streams (first layer)
     const StreamDesc* streams;
     int n_streams;
@@ -83,6 +84,7 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     const int b = tile / p.tiles_per_window;
     const int t0 = (tile - b * p.tiles_per_window) * kBM;
+    if (p.win_rows && t0 >= p.win_rows[b]) return;  // uniform over the block
     const int64_t row0 = (int64_t)b * p.T + t0;
 
     // ---- stage A = [x[t-d] | x[t]], t in [t0, t0 + 64); x[tau < 0] = 0 (zero window context)
@@ -299,6 +301,7 @@ hipError_t wavenet_layers_f32(gwd_model* m, const FwdBatch& fb, float* x_a, floa
         a.pre_out = nullptr;
         a.T = fb.T;
         a.tiles_per_window = tpw;
+        a.win_rows = fb.rows ? fb.rows + fb.win_base : nullptr;
         a.streams = fb.streams;
         a.n_streams = fb.n_streams;
         a.win_base = fb.win_base;

@@ -47,6 +47,7 @@ struct LayerArgsLP {
     const float* sc;     // FP8 conv column scales [256]
     const float* srs;    // FP8 res|skip column scales
     int d, T, tiles_per_window;
+    const int32_t* win_rows;  // per window: rows anyone needs (null: all T)
     const StreamDesc* streams;
     int n_streams;
     int64_t win_base;
@@ -211,6 +212,7 @@ void layer_lp_kernel(LayerArgsLP p) {
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     const int b = tile / p.tiles_per_window;
     const int t0 = (tile - b * p.tiles_per_window) * BM;
+    if (p.win_rows && t0 >= p.win_rows[b]) return;  // uniform over the block
     const int64_t row0 = (int64_t)b * p.T + t0;
 
     // ---- stage A = [x[t-d] | x[t]]: BM rows x 2 taps x 16 chunks of 8 channels
@@ -465,6 +467,7 @@ struct FusedArgs {
     const float* srs[FU_MAXL];   // FP8: res|skip column scales [256]
     int d0, T;             // dilation of the first layer; window length
     int n_seg, seg_chunks; // segments per sub-sequence, chunks per segment
+    const int32_t* win_rows;  // per window of the launch: rows anyone needs (null: all T)
     const StreamDesc* streams;
     int n_streams;
     int64_t win_base;
@@ -734,8 +737,19 @@ static hipError_t launch_fused(gwd_model* m, int member, int l, int nl, const ui
     // first costs one warm-up chunk; the autotuner may aim at more blocks (gwd_set_fused_blocks)
     const int64_t per = (int64_t)nb * a.d0;
     const int64_t target = m->fused_blocks > 0 ? m->fused_blocks : 512;
-    const int want = (int)std::min<int64_t>(n_ch, std::max<int64_t>(1, (target + per - 1) / per));
-    a.seg_chunks = (n_ch + want - 1) / want;
+    if (fb && fb->h_rows) {
+        // merged windows differ in length: the chunks in use are shared out over the blocks
+        a.win_rows = fb->rows + fb->win_base;
+        int64_t chunks = 0;
+        for (int i = 0; i < nb; ++i) {
+            const int64_t sub = (fb->h_rows[fb->win_base + i] + a.d0 - 1) / a.d0;
+            chunks += a.d0 * ((sub + rows - 1) / rows);
+        }
+        a.seg_chunks = (int)std::min<int64_t>(n_ch, std::max<int64_t>(1, (chunks + target - 1) / target));
+    } else {
+        const int want = (int)std::min<int64_t>(n_ch, std::max<int64_t>(1, (target + per - 1) / per));
+        a.seg_chunks = (n_ch + want - 1) / want;
+    }
     a.n_seg = (n_ch + a.seg_chunks - 1) / a.seg_chunks;
     // the network's first layers take the stream (inference) or a bf16 x0 (training: fb == nullptr)
     const bool first = l == 0, stream_in = first && fb != nullptr;
@@ -845,6 +859,7 @@ static hipError_t layers_lp(gwd_model* m, const FwdBatch& fb, float* x_a, float*
         a.skip = skip;
         a.pre_out = nullptr;
         a.T = fb.T;
+        a.win_rows = fb.rows ? fb.rows + fb.win_base : nullptr;
         a.streams = fb.streams;
         a.n_streams = fb.n_streams;
         a.win_base = fb.win_base;

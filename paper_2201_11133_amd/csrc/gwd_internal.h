@@ -97,9 +97,11 @@ struct gwd_model {
     gwd::Workspace tws;                        // training workspace
     std::vector<void*> canon;                  // device copy of each member's canonical blob (fp32; fp64 for GWD_FP64)
     int32_t batch_windows;                     // windows per layer-kernel batch
+    bool merge_windows = true;                 // stitched forwards on merged windows (gwd_set_window_merging)
     int32_t last_nb = 0, last_T = 0;           // batch shape of the last gwd_forward (workspace contents)
     int64_t ws_tab_bytes = 0;                  // bytes reserved for the stream table at the workspace start
     std::vector<int64_t> host_firsts;          // host copy of FwdBatch::firsts for the current request
+    std::vector<int32_t> host_rows;            // host copy of FwdBatch::rows for the current request (empty: none)
     int32_t lp_rows = 0;                       // BF16/FP8 layer tiling: rows per tile (0 = default per precision)
     int32_t lp_waves = 0;                      // and waves per block
     int32_t lp_fuse = 3;                       // BF16/FP8: layers per launch (3 = fused triples and quads, 6 = sextets and quads, 1 = one per launch)
@@ -148,6 +150,8 @@ struct FwdBatch {
     float* out;
     int64_t sum_L;      // total samples (stitched layout)
     int64_t total_win;  // total windows (mode 2 layout)
+    const int32_t* rows;    // device, per global window: rows whose values anyone needs (null: all T)
+    const int32_t* h_rows;  // the same on the host
     const int64_t* firsts;  // device: global index of each stream's first window (streams with windows)
     int64_t first_idx;      // first entry of `firsts` inside this batch
     int n_first;            // entries of `firsts` inside this batch

@@ -211,6 +211,13 @@ gwd_status gwd_set_persistent(gwd_model* m, int32_t on) {
     return GWD_OK;
 }
 
+gwd_status gwd_set_window_merging(gwd_model* m, int32_t on) {
+    if (!m) { set_error("gwd_set_window_merging: model is NULL"); return GWD_ERR_ARG; }
+    if (on != 0 && on != 1) { set_error("gwd_set_window_merging: on must be 0 or 1"); return GWD_ERR_ARG; }
+    m->merge_windows = on != 0;
+    return GWD_OK;
+}
+
 namespace {
 struct Sched {
     int rows, waves, fuse, blocks, persist;

@@ -108,6 +108,7 @@ def _load(path: str = LIB_PATH):
         "gwd_set_tiling": (I32, [P, I32, I32, I32, I32]),
         "gwd_set_fused_blocks": (I32, [P, I32]),
         "gwd_set_persistent": (I32, [P, I32]),
+        "gwd_set_window_merging": (I32, [P, I32]),
         "gwd_autotune": (I32, [P, ctypes.POINTER(Stream), I32, I32, I32, P, I64, ctypes.POINTER(I32),
                                ctypes.POINTER(I32), ctypes.POINTER(I32), ctypes.POINTER(I32), ctypes.POINTER(I32),
                                ctypes.POINTER(I32), P]),
@@ -245,6 +246,11 @@ class Model:
     def set_persistent(self, on: bool = True):
         """gwd_set_persistent: run the forward (and plans created afterwards) as one persistent launch."""
         check(lib.gwd_set_persistent(self.h, 1 if on else 0))
+
+    def set_window_merging(self, on: bool = True):
+        """gwd_set_window_merging: stitched scores from merged windows (the default), or from every row of
+        every window of the request."""
+        check(lib.gwd_set_window_merging(self.h, 1 if on else 0))
 
     def autotune(self, streams, window: int = 4096, stride: int = 256, out=None, stream=None):
         """Pick the fastest schedule for this request; returns (tile_rows, waves, layers_per_launch,

@@ -1,0 +1,48 @@
+"""Stitched forwards on merged windows equal the request's own windows bit for bit."""
+import numpy as np
+import pytest
+
+from tests.gpu_common import to_dev
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+# stream lengths: one sample, the edges of tiles, of the receptive field and of a window, several
+# merged windows in one stream, ragged sets with an empty stream
+LENGTHS = [[1], [127, 128, 129], [3069, 3070, 3071], [4096], [4097, 0, 64], [30000], [131, 61234, 9000, 0, 4095]]
+
+
+@pytest.fixture(scope="module")
+def g():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2201_11133_amd import gwd
+    return gwd
+
+
+@pytest.mark.parametrize("prec,two", [("fp32", False), ("bf16", False), ("fp8", False), ("bf16", True)])
+def test_merged_windows_give_the_same_scores(g, prec, two):
+    from paper_2201_11133_amd import synth
+    make = synth.two_branch_weights if two else synth.full_weights
+    m = g.Model(g.two_branch_arch() if two else g.full_arch(), np.stack([make(41), make(42)]), prec)
+    for i, lens in enumerate(LENGTHS):
+        xs = [to_dev(synth.make_stream(500 + 10 * i + j, max(L, 1) / 4096, 0)[0][:L]) if L
+              else torch.zeros((0, 2), device="cuda") for j, L in enumerate(lens)]
+        if i % 2:   # planar streams
+            xs = [(x[:, 0].contiguous(), x[:, 1].contiguous()) for x in xs]
+        for W, S in ((4096, 256), (3200, 128), (8192, 1000)):
+            for batch in (1, 7, 512):   # the batch bounds the merged windows' rows
+                for fuse in ((1,) if prec == "fp32" else (1, 3, 6)):
+                    m.set_tiling(0, 0, batch, fuse)
+                    m.set_window_merging(False)
+                    ref = m.forward(xs, W, S, 1).clone()
+                    m.set_window_merging(True)
+                    print(f"case: {prec} {lens} W={W} S={S} batch={batch} fuse={fuse}", flush=True)
+                    assert torch.equal(m.forward(xs, W, S, 1), ref)
+                    if batch == 7:
+                        assert torch.equal(m.forward(xs, W, S, 0), ref[: sum(lens)])
+                        plan = m.plan(xs, W, S, 1)
+                        assert torch.equal(plan.launch(), ref)
+                        plan.close()
+    assert g.lib.gwd_set_window_merging(m.h, 2) == g.ERR_ARG and g.lib.gwd_set_window_merging(None, 1) == g.ERR_ARG
+    m.close()
