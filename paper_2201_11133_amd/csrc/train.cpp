@@ -374,23 +374,17 @@ gwd_status gwd_backward(gwd_model* m, int32_t member, const float* windows, int3
     hipError_t e = hipSetDevice(m->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     if (m->arch.kind == 0) {
-        const int64_t M = (int64_t)B * W;
         const size_t es = m->prec == GWD_FP64 ? 8 : 4;
-        s = ensure_tws(m, 2 * M * 16 * (int64_t)es, st);
+        s = ensure_tws(m, tiny_train_backward_scratch(B, W) * (int64_t)es, st);
         if (s != GWD_OK) return s;
-        if (m->prec == GWD_FP64) {
-            e = hipMemsetAsync(grad_params, 0, m->n_params * 8, st);
-            if (e == hipSuccess)
-                e = tiny_train_backward<double>((const double*)m->canon[member], windows, B, W, (const double*)saved,
-                                                (const double*)grad_logit, (double*)grad_params, (double*)m->tws.base,
-                                                (double*)grad_input, st);
-        } else {
-            e = hipMemsetAsync(grad_params, 0, m->n_params * 4, st);
-            if (e == hipSuccess)
-                e = tiny_train_backward<float>((const float*)m->canon[member], windows, B, W, (const float*)saved,
-                                               (const float*)grad_logit, (float*)grad_params, (float*)m->tws.base,
-                                               (float*)grad_input, st);
-        }
+        if (m->prec == GWD_FP64)
+            e = tiny_train_backward<double>((const double*)m->canon[member], windows, B, W, (const double*)saved,
+                                            (const double*)grad_logit, (double*)grad_params, (double*)m->tws.base,
+                                            (double*)grad_input, st);
+        else
+            e = tiny_train_backward<float>((const float*)m->canon[member], windows, B, W, (const float*)saved,
+                                           (const float*)grad_logit, (float*)grad_params, (float*)m->tws.base,
+                                           (float*)grad_input, st);
         return e == hipSuccess ? GWD_OK : hip_fail(e, "small member backward");
     }
     if (m->two_branch) {

@@ -128,8 +128,9 @@ hipError_t launch_bce(const float* z, const float* y, int64_t n, float* grad, do
 template <class T>
 hipError_t tiny_train_forward(const T* blob, const float* u, int B, int Tw, T* ys /*[4][M][16]*/, T* logits,
                               hipStream_t st);
+int64_t tiny_train_backward_scratch(int B, int Tw);   // values of T the backward needs as scratch
 template <class T>
 hipError_t tiny_train_backward(const T* blob, const float* u, int B, int Tw, const T* ys, const T* dz, T* grad,
-                               T* dbuf /*[2][M][16]*/, T* du, hipStream_t st);
+                               T* scratch, T* du, hipStream_t st);
 
 }  // namespace gwd

@@ -1,156 +1,415 @@
 // Training of the small plain member (four causal convolutions, 16 channels, ReLU, 1x1 to a logit)
 // in float or double; double is used for the finite-difference gradient check on the device.
+//
+// The member is 3,232 flop per time step, so a step is bound by launches and latency, not by
+// arithmetic (64 windows: 2.5 GFLOP with the backward, 16 us at the fp32 matrix rate). Both passes
+// keep one time step per thread and carry it through all four layers in one kernel: a row's 16
+// channels stay in registers, LDS holds only what neighbouring rows read (the dilation taps), and the
+// weights, the same for every lane, are scalar operands. A tile recomputes the few rows its
+// neighbours own (14 in the forward, 16 in the backward of 256), which costs less than a launch. The
+// weight gradients are sums over all rows in a fixed order, taken by a second kernel.
 #include "train_internal.h"
 
 namespace gwd {
 
 constexpr int TC = 16;
+constexpr int TN = 256;                   // threads (time steps) per tile
+constexpr int TF_HALO = 14;               // forward: rows left of the tile (dilations 2 + 4 + 8)
+constexpr int TF_ROWS = TN - TF_HALO;
+constexpr int TB_HALO = 16;               // backward: rows right of the tile (8 + 4 + 2 + 1, rounded)
+constexpr int TB_ROWS = TN - TB_HALO;
+constexpr int T_PARAMS = 80 + 3 * 528 + 17;
+constexpr int T_RES = 256;                // weight gradients: partial sums by row index mod 256
 
 // blob offsets: conv0 (W [16][2][2], b [16]) = 80 values, conv1..3 (W [16][16][2], b) = 528 each, out W [16], b [1]
-__host__ __device__ inline int tiny_off(int layer) { return layer == 0 ? 0 : 80 + 528 * (layer - 1); }
-__host__ __device__ inline int tiny_cin(int layer) { return layer == 0 ? 2 : TC; }
+__host__ __device__ constexpr int tiny_off(int layer) { return layer == 0 ? 0 : 80 + 528 * (layer - 1); }
+__host__ __device__ constexpr int tiny_cin(int layer) { return layer == 0 ? 2 : TC; }
 
+// LDS rows of 16 channels, padded so that 16-byte accesses of consecutive rows spread over the banks.
 template <class T>
-__device__ inline T in_val(const float* u, const T* y, int layer, int64_t row, int c) {
-    return layer == 0 ? (T)u[2 * row + c] : y[row * TC + c];
-}
+constexpr int tiny_ld() { return TC + 16 / (int)sizeof(T); }
 
-// out[row][o] = ReLU(b[o] + sum_c W[o][c][0] in[t - d][c] + W[o][c][1] in[t][c]), zero context
+// The 16 channels of one row, as 16-byte accesses (LDS rows, and rows of ys: 4-byte aligned is enough
+// for global memory).
 template <class T>
-__global__ __launch_bounds__(256) void tiny_conv_fwd(const T* blob, const float* u, const T* yin, int layer,
-                                                     int64_t M, int Tw, T* yout) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * TC) return;
-    const int64_t row = i / TC;
-    const int o = (int)(i % TC);
-    const int t = (int)(row % Tw);
-    const int d = 1 << layer, cin = tiny_cin(layer);
-    const T* W = blob + tiny_off(layer);
-    const T* b = W + TC * cin * 2;
-    T acc = b[o];
-    for (int c = 0; c < cin; ++c) {
-        if (t - d >= 0) acc += W[(o * cin + c) * 2 + 0] * in_val<T>(u, yin, layer, row - d, c);
-        acc += W[(o * cin + c) * 2 + 1] * in_val<T>(u, yin, layer, row, c);
+__device__ inline void load_row(const T* p, T (&v)[TC]) {
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int E = 16 / sizeof(T);
+#pragma unroll
+    for (int i = 0; i < TC / E; ++i) {
+        const vec x = *(const vec*)(p + E * i);
+#pragma unroll
+        for (int j = 0; j < E; ++j) v[E * i + j] = x[j];
     }
-    yout[i] = acc > (T)0 ? acc : (T)0;
 }
-
 template <class T>
-__global__ __launch_bounds__(256) void tiny_out_fwd(const T* blob, const T* y4, int64_t M, T* z) {
-    const int64_t row = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (row >= M) return;
-    const T* w = blob + tiny_off(4);
-    T s = w[TC];
-    for (int c = 0; c < TC; ++c) s += w[c] * y4[row * TC + c];
-    z[row] = s;
-}
-
-// One block per output parameter: grad[p] += sum over rows of term(row), tree-reduced in a fixed order.
-// kind 0: conv weight (layer, o, c, tap); 1: conv bias (layer, o); 2: out weight c; 3: out bias
-template <class T>
-__global__ __launch_bounds__(256) void tiny_param_grad(const T* blob, const float* u, const T* ys, const T* dpre,
-                                                       const T* dz, int layer, int64_t M, int Tw, T* grad) {
-    __shared__ T red[256];
-    const int pidx = blockIdx.x;   // parameter index within the layer's (W, b) block, or out block
-    T s = 0;
-    if (layer < 4) {
-        const int cin = tiny_cin(layer), d = 1 << layer;
-        const int nW = TC * cin * 2;
-        const T* yin = layer == 0 ? nullptr : ys + (int64_t)(layer - 1) * M * TC;
-        if (pidx < nW) {
-            const int o = pidx / (cin * 2), c = (pidx / 2) % cin, tap = pidx % 2;
-            for (int64_t row = threadIdx.x; row < M; row += 256) {
-                const int t = (int)(row % Tw);
-                const int64_t src = tap == 0 ? row - d : row;
-                if (tap == 0 && t - d < 0) continue;
-                s += dpre[row * TC + o] * in_val<T>(u, yin, layer, src, c);
-            }
-        } else {
-            const int o = pidx - nW;
-            for (int64_t row = threadIdx.x; row < M; row += 256) s += dpre[row * TC + o];
-        }
-    } else {
-        const T* y4 = ys + 3 * M * TC;
-        for (int64_t row = threadIdx.x; row < M; row += 256) s += dz[row] * (pidx < TC ? y4[row * TC + pidx] : (T)1);
+__device__ inline void store_row(T* p, const T (&v)[TC]) {
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    constexpr int E = 16 / sizeof(T);
+#pragma unroll
+    for (int i = 0; i < TC / E; ++i) {
+        vec x;
+#pragma unroll
+        for (int j = 0; j < E; ++j) x[j] = v[E * i + j];
+        *(vec*)(p + E * i) = x;
     }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) grad[(layer < 4 ? tiny_off(layer) : tiny_off(4)) + pidx] += red[0];
 }
 
-// dy4[row][c] = dz[row] w_out[c]
-template <class T>
-__global__ __launch_bounds__(256) void tiny_out_bwd(const T* blob, const T* dz, int64_t M, T* dy) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * TC) return;
-    dy[i] = dz[i / TC] * blob[tiny_off(4) + (int)(i % TC)];
-}
-
-// dpre = dy * (y > 0)
-template <class T>
-__global__ __launch_bounds__(256) void tiny_relu_bwd(const T* dy, const T* y, int64_t n, T* dpre) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) dpre[i] = y[i] > (T)0 ? dy[i] : (T)0;
-}
-
-// din[row][c] = sum_o dpre[row][o] W[o][c][1] + dpre[row + d][o] W[o][c][0]   (row + d inside the window)
-template <class T>
-__global__ __launch_bounds__(256) void tiny_conv_dgrad(const T* blob, const T* dpre, int layer, int64_t M, int Tw,
-                                                       T* din, int cin_out) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * cin_out) return;
-    const int64_t row = i / cin_out;
-    const int c = (int)(i % cin_out);
-    const int t = (int)(row % Tw);
-    const int d = 1 << layer, cin = tiny_cin(layer);
-    const T* W = blob + tiny_off(layer);
-    T s = 0;
+// acc[o] = b[o] + sum_c (W[o][c][0] xo[c] + W[o][c][1] xc[c]), channel by channel, the tap at t - d
+// only where it lies inside the window (`tap`). An output's weights are consecutive: wide scalar loads.
+template <class T, int CIN>
+__device__ inline void tiny_conv(const T* __restrict__ W, const T (&xo)[CIN], const T (&xc)[CIN], bool tap, T (&acc)[TC]) {
+    const T* b = W + TC * CIN * 2;
+#pragma unroll
     for (int o = 0; o < TC; ++o) {
-        s += dpre[row * TC + o] * W[(o * cin + c) * 2 + 1];
-        if (t + d < Tw) s += dpre[(row + d) * TC + o] * W[(o * cin + c) * 2 + 0];
+        T s = b[o];
+#pragma unroll
+        for (int c = 0; c < CIN; ++c) {
+            const T far = s + W[(o * CIN + c) * 2 + 0] * xo[c];
+            s = tap ? far : s;
+            s += W[(o * CIN + c) * 2 + 1] * xc[c];
+        }
+        acc[o] = s;
     }
-    din[i] = s;
 }
 
-static inline unsigned nb(int64_t n) { return (unsigned)((n + 255) / 256); }
+// Layer outputs ys [4][M][16] and logits z [M] of windows u [M][2]. Block: one tile of TF_ROWS rows of
+// one window, thread tid the row t0 - TF_HALO + tid. 64 windows of 4096: 744 us (one launch per layer,
+// one output per thread, every weight a vector load) -> 46 us.
+template <class T>
+__global__ __launch_bounds__(TN) void tiny_fwd_kernel(const T* __restrict__ blob, const float* __restrict__ u,
+                                                      int64_t M, int Tw, int tiles, T* __restrict__ ys, T* __restrict__ z) {
+    constexpr int LD = tiny_ld<T>();
+    __shared__ __attribute__((aligned(16))) T y[2][TN][LD];
+    const int tid = threadIdx.x;
+    const int64_t b = blockIdx.x / tiles;
+    const int t = (int)(blockIdx.x - b * tiles) * TF_ROWS - TF_HALO + tid;
+    const bool in = t >= 0 && t < Tw, own = in && tid >= TF_HALO;
+    const int64_t row = b * Tw + t;
+    T acc[TC];
+    {
+        T xc[2] = {}, xo[2] = {};
+        if (in) {
+            xc[0] = (T)u[2 * row];
+            xc[1] = (T)u[2 * row + 1];
+            if (t >= 1) {
+                xo[0] = (T)u[2 * row - 2];
+                xo[1] = (T)u[2 * row - 1];
+            }
+        }
+        tiny_conv<T, 2>(blob, xo, xc, t >= 1, acc);
+    }
+#pragma unroll
+    for (int layer = 0; layer < 4; ++layer) {
+#pragma unroll
+        for (int o = 0; o < TC; ++o) acc[o] = acc[o] > (T)0 ? acc[o] : (T)0;
+        if (own) store_row(ys + ((int64_t)layer * M + row) * TC, acc);
+        if (layer == 3) break;
+        store_row(y[layer & 1][tid], acc);
+        __syncthreads();
+        const int d = 2 << layer;
+        T xo[TC], xc[TC];
+        load_row(y[layer & 1][tid >= d ? tid - d : 0], xo);   // (rows left of the halo feed halo rows only)
+#pragma unroll
+        for (int o = 0; o < TC; ++o) xc[o] = acc[o];
+        tiny_conv<T, TC>(blob + tiny_off(layer + 1), xo, xc, t >= d, acc);
+    }
+    if (own) {
+        const T* w = blob + tiny_off(4);
+        T s = w[TC];
+#pragma unroll
+        for (int c = 0; c < TC; ++c) s += w[c] * acc[c];
+        z[row] = s;
+    }
+}
+
+// dL/dpre of every layer dp [4][M][16] and, if du, dL/dwindows. Block: one tile of TB_ROWS rows of one
+// window, thread tid the row t0 + tid, the layers in reverse with dL/dpre of its row in registers and, for
+// the taps of the rows to the left, in LDS. 64 windows of 4096: 295 us (three launches per layer) -> 37 us.
+template <class T>
+__global__ __launch_bounds__(TN) void tiny_bwd_kernel(const T* __restrict__ blob, const T* __restrict__ ys,
+                                                      const T* __restrict__ dz, int64_t M, int Tw, int tiles,
+                                                      T* __restrict__ du, T* __restrict__ dpre) {
+    constexpr int LD = tiny_ld<T>();
+    __shared__ __attribute__((aligned(16))) T D[2][TN][LD];
+    const int tid = threadIdx.x;
+    const int64_t b = blockIdx.x / tiles;
+    const int t = (int)(blockIdx.x - b * tiles) * TB_ROWS + tid;
+    const bool in = t < Tw, own = in && tid < TB_ROWS;
+    const int64_t row = b * Tw + t;
+    // rows past the window: their loads read the window's last row, their dL/dpre is zero
+    const int64_t lrow = in ? row : b * Tw + Tw - 1;
+    T y[TC], dp[TC];
+    {
+        const T g = dz[lrow];
+        load_row(ys + ((int64_t)3 * M + lrow) * TC, y);
+        const T* wo = blob + tiny_off(4);
+#pragma unroll
+        for (int c = 0; c < TC; ++c) {
+            const T v = g * wo[c];
+            dp[c] = in && y[c] > (T)0 ? v : (T)0;
+        }
+    }
+#pragma unroll
+    for (int layer = 3; layer >= 1; --layer) {
+        const int d = 1 << layer;
+        store_row(D[layer & 1][tid], dp);
+        if (own) store_row(dpre + ((int64_t)layer * M + row) * TC, dp);
+        load_row(ys + ((int64_t)(layer - 1) * M + lrow) * TC, y);
+        __syncthreads();
+        // dL/dy of the layer below, then through its ReLU
+        const T* W = blob + tiny_off(layer);
+        const bool tap = t + d < Tw;
+        T dn[TC];
+        load_row(D[layer & 1][tid + d < TN ? tid + d : TN - 1], dn);   // (past the halo: rows nobody uses)
+        T s[TC] = {}, w[2 * TC], wn[2 * TC];   // an output's weights are consecutive: wide scalar loads
+#pragma unroll
+        for (int i = 0; i < 2 * TC; ++i) wn[i] = W[i];
+#pragma unroll
+        for (int o = 0; o < TC; ++o) {
+#pragma unroll
+            for (int i = 0; i < 2 * TC; ++i) w[i] = wn[i];
+            if (o + 1 < TC) {
+#pragma unroll
+                for (int i = 0; i < 2 * TC; ++i) wn[i] = W[(o + 1) * 2 * TC + i];
+            }
+            __builtin_amdgcn_sched_barrier(0);   // one output's weights in flight during the one before
+#pragma unroll
+            for (int c = 0; c < TC; ++c) {
+                s[c] += dp[o] * w[2 * c + 1];
+                const T both = s[c] + dn[o] * w[2 * c];
+                s[c] = tap ? both : s[c];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int c = 0; c < TC; ++c) dp[c] = in && y[c] > (T)0 ? s[c] : (T)0;
+    }
+    if (own) store_row(dpre + row * TC, dp);
+    if (!du) return;
+    store_row(D[0][tid], dp);
+    __syncthreads();
+    if (own) {
+        T s0 = 0, s1 = 0;
+        const bool tap = t + 1 < Tw;
+#pragma unroll
+        for (int o = 0; o < TC; ++o) {
+            s0 += dp[o] * blob[4 * o + 1];
+            s1 += dp[o] * blob[4 * o + 3];
+            if (tap) {
+                s0 += D[0][tid + 1][o] * blob[4 * o + 0];
+                s1 += D[0][tid + 1][o] * blob[4 * o + 2];
+            }
+        }
+        du[2 * row] = s0;
+        du[2 * row + 1] = s1;
+    }
+}
+
+// Weight gradients, first level: part[j][p] = sum over the rows r = j (mod T_RES), in ascending order, of
+// parameter p's term: a serial chain over M / 256 rows for each of 256 x 1,681 sums. Block (group, four
+// consecutive residues j, one per wave): groups 0-2 the conv layers 1-3, lane (o pair, c pair) of both taps,
+// group 3 conv 0 and the output layer. T_STEP steps (64 rows) of each operand go through LDS as one 16-byte
+// load per thread, T_DEEP stages ahead: with every lane loading its own operands the vector-memory
+// instructions bounded it. 64 windows of 4096: 2,660 us (one block per parameter walking every row),
+// 337 us with a block per residue reading its operands directly, 105 us now; the 200 MB it reads
+// take 40 us at the rate of a large copy.
+constexpr int T_STEP = 16, T_DEEP = 3;
+
+// Stage `st` of one operand with 16 channels (rows r - back): registers, then LDS [64 rows][16].
+template <class T>
+struct TinyStage {
+    typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+    static constexpr int NV = sizeof(T) / 4;
+    vec v[NV];
+    __device__ void load(const T* __restrict__ src, int st, int j0, int back, int64_t M, int tid) {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) {
+            const int e = (tid + 256 * k) * (16 / (int)sizeof(T)), q = e / TC;
+            const int64_t r = (int64_t)T_RES * (st * T_STEP + (q >> 2)) + j0 + (q & 3) - back;
+            v[k] = *(const vec*)(src + min(max(r, (int64_t)0), M - 1) * TC + e % TC);   // (rows outside are not added)
+        }
+    }
+    __device__ void store(T* lds, int tid) const {
+#pragma unroll
+        for (int k = 0; k < NV; ++k) *(vec*)(lds + (tid + 256 * k) * (16 / (int)sizeof(T))) = v[k];
+    }
+};
+
+template <class T>
+__global__ __launch_bounds__(256) void tiny_wgrad_kernel(const float* __restrict__ u, const T* __restrict__ ys,
+                                                         const T* __restrict__ dpre, const T* __restrict__ dz, int64_t M,
+                                                         int Tw, T* __restrict__ part) {
+    constexpr int SZ = T_STEP * 4 * TC;
+    __shared__ __attribute__((aligned(16))) T sd[2][SZ], sx[2][SZ], so[2][SZ];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int group = blockIdx.x & 3, j0 = 4 * (blockIdx.x >> 2), j = j0 + wave;
+    T* out = part + (int64_t)j * T_PARAMS;
+    const int64_t n = M > j ? (M - j + T_RES - 1) / T_RES : 0;                       // rows of this wave's residue
+    const int nst = (int)((M > j0 ? (M - j0 + T_RES - 1) / T_RES : 0) + T_STEP - 1) / T_STEP;   // stages (uniform)
+    int t = j % Tw;                                // time step of the row being added
+    const int step = T_RES % Tw;
+    if (group < 3) {
+        const int layer = group + 1, d = 1 << layer, o = 2 * (lane >> 3), c = 2 * (lane & 7);
+        const T* D = dpre + (int64_t)layer * M * TC;
+        const T* X = ys + (int64_t)(layer - 1) * M * TC;
+        TinyStage<T> pd[T_DEEP], px[T_DEEP], po[T_DEEP];
+        auto load = [&](int k, int st) __attribute__((always_inline)) {
+            pd[k].load(D, st, j0, 0, M, tid);
+            px[k].load(X, st, j0, 0, M, tid);
+            po[k].load(X, st, j0, d, M, tid);
+        };
+        T a[2][2][2] = {}, ab[2] = {};             // [o][c][tap], biases
+#pragma unroll
+        for (int k = 0; k < T_DEEP; ++k) load(k, k);
+        for (int st0 = 0; st0 < nst; st0 += T_DEEP)
+#pragma unroll
+            for (int k = 0; k < T_DEEP; ++k) {
+                const int st = st0 + k, bf = st & 1;
+                if (st >= nst) break;              // uniform over the block
+                pd[k].store(sd[bf], tid);
+                px[k].store(sx[bf], tid);
+                po[k].store(so[bf], tid);
+                __syncthreads();                   // (the other buffer is read before its next store's barrier)
+                load(k, st + T_DEEP);
+                const int rows = (int)min((int64_t)T_STEP, n - (int64_t)st * T_STEP);
+                auto add = [&](int i) __attribute__((always_inline)) {
+                    const int q = (4 * i + wave) * TC;
+                    const T d0 = sd[bf][q + o], d1 = sd[bf][q + o + 1];
+                    const T x0 = sx[bf][q + c], x1 = sx[bf][q + c + 1];
+                    const T y0 = so[bf][q + c], y1 = so[bf][q + c + 1];
+                    const bool tap = t >= d;       // uniform over the wave
+                    const T s00 = a[0][0][0] + d0 * y0, s01 = a[0][1][0] + d0 * y1;
+                    const T s10 = a[1][0][0] + d1 * y0, s11 = a[1][1][0] + d1 * y1;
+                    a[0][0][0] = tap ? s00 : a[0][0][0];
+                    a[0][1][0] = tap ? s01 : a[0][1][0];
+                    a[1][0][0] = tap ? s10 : a[1][0][0];
+                    a[1][1][0] = tap ? s11 : a[1][1][0];
+                    a[0][0][1] += d0 * x0;
+                    a[0][1][1] += d0 * x1;
+                    a[1][0][1] += d1 * x0;
+                    a[1][1][1] += d1 * x1;
+                    ab[0] += d0;
+                    ab[1] += d1;
+                    t += step;
+                    t -= t >= Tw ? Tw : 0;
+                };
+                if (rows == T_STEP) {              // whole stages unrolled: later rows' LDS reads overlap the sums
+#pragma unroll
+                    for (int i = 0; i < T_STEP; ++i) add(i);
+                } else {
+                    for (int i = 0; i < rows; ++i) add(i);
+                }
+            }
+        T* w = out + tiny_off(layer);
+#pragma unroll
+        for (int oi = 0; oi < 2; ++oi) {
+#pragma unroll
+            for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+                for (int tap = 0; tap < 2; ++tap) w[((o + oi) * TC + c + ci) * 2 + tap] = a[oi][ci][tap];
+            if (c == 0) w[TC * TC * 2 + o + oi] = ab[oi];
+        }
+        return;
+    }
+    // conv 0: lane (o, c, tap) a weight; the output layer and the biases: lanes 0-15 conv 0's biases,
+    // 16-31 the output weights, 32 their bias. so: [64 rows] dz, u(t) and u(t - 1).
+    TinyStage<T> pd[T_DEEP], py[T_DEEP];
+    T pz[T_DEEP][5];
+    auto load = [&](int k, int st) __attribute__((always_inline)) {
+        pd[k].load(dpre, st, j0, 0, M, tid);
+        py[k].load(ys + 3 * M * TC, st, j0, 0, M, tid);
+        const int64_t r = min((int64_t)T_RES * (st * T_STEP + (lane >> 2)) + j0 + (lane & 3), M - 1);
+        const int64_t rp = max(r - 1, (int64_t)0);
+        pz[k][0] = dz[r];
+        pz[k][1] = (T)u[2 * r];
+        pz[k][2] = (T)u[2 * r + 1];
+        pz[k][3] = (T)u[2 * rp];
+        pz[k][4] = (T)u[2 * rp + 1];
+    };
+    const int o = lane >> 2, c = (lane >> 1) & 1, tap = lane & 1;
+    T a0 = 0, a1 = 0;
+#pragma unroll
+    for (int k = 0; k < T_DEEP; ++k) load(k, k);
+    for (int st0 = 0; st0 < nst; st0 += T_DEEP)
+#pragma unroll
+        for (int k = 0; k < T_DEEP; ++k) {
+            const int st = st0 + k, bf = st & 1;
+            if (st >= nst) break;
+            pd[k].store(sd[bf], tid);
+            py[k].store(sx[bf], tid);
+            if (tid < 64)
+#pragma unroll
+                for (int e = 0; e < 5; ++e) so[bf][8 * tid + e] = pz[k][e];
+            __syncthreads();
+            load(k, st + T_DEEP);
+            const int rows = (int)min((int64_t)T_STEP, n - (int64_t)st * T_STEP);
+            auto add = [&](int i) __attribute__((always_inline)) {
+                const int q = 4 * i + wave;
+                const T z = so[bf][8 * q];
+                const T dv = sd[bf][q * TC + o], xv = so[bf][8 * q + (tap ? 1 : 3) + c];
+                const T s0 = a0 + dv * xv;
+                a0 = tap || t >= 1 ? s0 : a0;
+                // one multiply-add for all three sums (a product with 1 is exact)
+                const T p0 = lane < 16 ? sd[bf][q * TC + (lane & 15)] : z;
+                const T p1 = lane >= 16 && lane < 32 ? sx[bf][q * TC + (lane & 15)] : (T)1;
+                a1 += p0 * p1;
+                t += step;
+                t -= t >= Tw ? Tw : 0;
+            };
+            if (rows == T_STEP) {
+#pragma unroll
+                for (int i = 0; i < T_STEP; ++i) add(i);
+            } else {
+                for (int i = 0; i < rows; ++i) add(i);
+            }
+        }
+    out[lane] = a0;
+    if (lane < 16) out[64 + lane] = a1;
+    else if (lane < 33) out[tiny_off(4) + lane - 16] = a1;
+}
+
+// grad[p] = the residues' sums added pairwise (j + 128, + 64, .. + 1).
+template <class T>
+__global__ __launch_bounds__(256) void tiny_reduce_kernel(const T* __restrict__ part, T* __restrict__ grad) {
+    __shared__ T red[16][16];
+    const int p = threadIdx.x & 15, run = threadIdx.x >> 4, i = blockIdx.x * 16 + p;
+    T v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[k] = i < T_PARAMS ? part[(int64_t)(run + 16 * k) * T_PARAMS + i] : (T)0;
+#pragma unroll
+    for (int w = 8; w > 0; w >>= 1)
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (k < w) v[k] += v[k + w];
+    red[run][p] = v[0];
+    for (int w = 8; w > 0; w >>= 1) {
+        __syncthreads();
+        if (run < w) red[run][p] += red[run + w][p];
+    }
+    if (run == 0 && i < T_PARAMS) grad[i] = red[0][p];
+}
+
+int64_t tiny_train_backward_scratch(int B, int Tw) { return 4 * (int64_t)B * Tw * TC + T_RES * T_PARAMS; }
 
 template <class T>
 hipError_t tiny_train_forward(const T* blob, const float* u, int B, int Tw, T* ys, T* logits, hipStream_t st) {
-    const int64_t M = (int64_t)B * Tw;
-    for (int l = 0; l < 4; ++l) {
-        const T* yin = l == 0 ? nullptr : ys + (int64_t)(l - 1) * M * TC;
-        hipLaunchKernelGGL(tiny_conv_fwd<T>, dim3(nb(M * TC)), dim3(256), 0, st, blob, u, yin, l, M, Tw,
-                           ys + (int64_t)l * M * TC);
-    }
-    hipLaunchKernelGGL(tiny_out_fwd<T>, dim3(nb(M)), dim3(256), 0, st, blob, ys + 3 * M * TC, M, logits);
+    const int tiles = (Tw + TF_ROWS - 1) / TF_ROWS;
+    hipLaunchKernelGGL(tiny_fwd_kernel<T>, dim3((unsigned)((int64_t)B * tiles)), dim3(TN), 0, st, blob, u,
+                       (int64_t)B * Tw, Tw, tiles, ys, logits);
     return hipGetLastError();
 }
 
 template <class T>
 hipError_t tiny_train_backward(const T* blob, const float* u, int B, int Tw, const T* ys, const T* dz, T* grad,
-                               T* dbuf, T* du, hipStream_t st) {
+                               T* scratch, T* du, hipStream_t st) {
     const int64_t M = (int64_t)B * Tw;
-    T* dy = dbuf;
-    T* dpre = dbuf + M * TC;
-    hipLaunchKernelGGL(tiny_param_grad<T>, dim3(TC + 1), dim3(256), 0, st, blob, u, ys, (const T*)nullptr, dz, 4, M,
-                       Tw, grad);
-    hipLaunchKernelGGL(tiny_out_bwd<T>, dim3(nb(M * TC)), dim3(256), 0, st, blob, dz, M, dy);
-    for (int l = 3; l >= 0; --l) {
-        const int cin = tiny_cin(l);
-        hipLaunchKernelGGL(tiny_relu_bwd<T>, dim3(nb(M * TC)), dim3(256), 0, st, dy, ys + (int64_t)l * M * TC, M * TC,
-                           dpre);
-        hipLaunchKernelGGL(tiny_param_grad<T>, dim3(TC * cin * 2 + TC), dim3(256), 0, st, blob, u, ys, dpre, dz, l, M,
-                           Tw, grad);
-        if (l > 0) {
-            hipLaunchKernelGGL(tiny_conv_dgrad<T>, dim3(nb(M * TC)), dim3(256), 0, st, blob, dpre, l, M, Tw, dy, TC);
-        } else if (du) {
-            hipLaunchKernelGGL(tiny_conv_dgrad<T>, dim3(nb(M * 2)), dim3(256), 0, st, blob, dpre, 0, M, Tw, du, 2);
-        }
-    }
+    const int tiles = (Tw + TB_ROWS - 1) / TB_ROWS;
+    T* part = scratch + 4 * M * TC;
+    hipLaunchKernelGGL(tiny_bwd_kernel<T>, dim3((unsigned)((int64_t)B * tiles)), dim3(TN), 0, st, blob, ys, dz, M, Tw,
+                       tiles, du, scratch);
+    hipLaunchKernelGGL(tiny_wgrad_kernel<T>, dim3(T_RES), dim3(256), 0, st, u, ys, (const T*)scratch, dz, M, Tw, part);
+    hipLaunchKernelGGL(tiny_reduce_kernel<T>, dim3((T_PARAMS + 15) / 16), dim3(256), 0, st, (const T*)part, grad);
     return hipGetLastError();
 }
 
