@@ -9,7 +9,11 @@
 // whole tile, so a tile holds at most one trigger and it can only be the tile's earliest maximum m.
 // One block per tile finds m (block argmax), then, if e[m] >= thr, checks the parts of m's
 // neighbourhood outside the tile (each shorter than wc). A second single-block kernel compacts the
-// per-tile candidates in (stream, sample) order.
+// per-tile candidates in (stream, sample) order. The search is a few microseconds of reading, so what a
+// call costs is its launches and copies: two kernels, and one copy back with the count and the first
+// records. Tables of up to TRIG_ARG streams travel as a kernel argument, longer ones as a copy. 64 streams
+// of 4096 samples, with the forward of the small member: 174 us (three kernels, three copies) -> 147 us.
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -29,6 +33,20 @@ struct TrigRecord {
     int64_t sample;
     float logit;
     float prob;
+};
+
+constexpr int TRIG_ARG = 80;      // streams whose table fits the kernel argument
+constexpr int TRIG_FIRST = 512;   // records copied to the host with the count
+constexpr int64_t TRIG_NONE = -1, TRIG_BAD = -2;   // a tile without a trigger, with a non-finite score
+
+struct TrigTable {
+    const TrigStream* dev;        // device table, or null: arg
+    TrigStream arg[TRIG_ARG];
+};
+
+struct TrigHead {                 // followed by the records
+    int64_t count;
+    int64_t bad;                  // a non-finite score
 };
 
 __device__ inline int find_tile_stream(const TrigStream* s, int n, int64_t tile) {
@@ -59,28 +77,35 @@ __device__ inline float block_max(float v, float* red) {
     return r;
 }
 
-__global__ __launch_bounds__(256) void trig_tile_kernel(const float* __restrict__ e, const TrigStream* streams,
-                                                        int n_streams, int wc, double thr, int64_t* cand,
-                                                        int* nonfinite) {
+__global__ __launch_bounds__(256) void trig_tile_kernel(const float* __restrict__ e, TrigTable tab,
+                                                        int n_streams, int wc, double thr, int64_t* cand) {
     __shared__ float redv[4];
     __shared__ int64_t redi[4];
     __shared__ float redm[4];
     const int64_t tile = blockIdx.x;
+    const TrigStream* streams = tab.dev ? tab.dev : tab.arg;
     const TrigStream s = streams[find_tile_stream(streams, n_streams, tile)];
     const int64_t a0 = s.e_begin + (tile - s.tile_begin) * (int64_t)wc;
     const int64_t a1 = min(a0 + (int64_t)wc, s.e_end);
     float bv = -INFINITY;
     int64_t bi = INT64_MAX;
     bool bad = false;
-    for (int64_t a = a0 + threadIdx.x; a < a1; a += blockDim.x) {
-        const float v = e[a];
-        if (!isfinite(v)) bad = true;
-        if (v > bv) {  // indices increase along the loop: strict > keeps the earliest
-            bv = v;
-            bi = a;
+    constexpr int AHEAD = 8;   // loads in flight per thread
+    for (int64_t a = a0 + threadIdx.x; a < a1; a += 256 * AHEAD) {
+        float v[AHEAD];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) v[k] = e[min(a + 256 * k, a1 - 1)];
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {
+            if (a + 256 * k >= a1) break;
+            if (!isfinite(v[k])) bad = true;
+            if (v[k] > bv) {  // indices increase along the loop: strict > keeps the earliest
+                bv = v[k];
+                bi = a + 256 * k;
+            }
         }
     }
-    if (bad) atomicOr(nonfinite, 1);
+    bad = __syncthreads_or(bad);
     for (int off = 32; off > 0; off >>= 1) {
         const float v2 = __shfl_xor(bv, off);
         const int64_t i2 = __shfl_xor(bi, off);
@@ -96,35 +121,50 @@ __global__ __launch_bounds__(256) void trig_tile_kernel(const float* __restrict_
     int64_t mi = redi[0];
     for (int w = 1; w < 4; ++w) amax_combine(mv, mi, redv[w], redi[w]);
     // every thread now holds the tile's earliest maximum (mv, mi)
-    int64_t out = -1;
+    int64_t out = TRIG_NONE;
     if (mi != INT64_MAX && (double)mv >= thr) {
         // left: [max(begin, m - wc), a0) must stay strictly below; right: [a1, min(end, m + wc + 1)) at or below
         const int64_t l0 = max(s.e_begin, mi - (int64_t)wc);
         const int64_t r1 = min(s.e_end, mi + (int64_t)wc + 1);
         float lm = -INFINITY, rm = -INFINITY;
-        for (int64_t a = l0 + threadIdx.x; a < a0; a += blockDim.x) lm = fmaxf(lm, e[a]);
-        for (int64_t a = a1 + threadIdx.x; a < r1; a += blockDim.x) rm = fmaxf(rm, e[a]);
+        // both sides' loads in flight together (a side that ends early reads its last sample again)
+        const int64_t nl = a0 - l0, nr = r1 - a1;
+        for (int64_t a = threadIdx.x; a < max(nl, nr); a += 256 * AHEAD) {
+            float v[AHEAD], w[AHEAD];
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) {
+                v[k] = e[nl > 0 ? l0 + min(a + 256 * k, nl - 1) : mi];
+                w[k] = e[nr > 0 ? a1 + min(a + 256 * k, nr - 1) : mi];
+            }
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) {
+                if (nl > 0) lm = fmaxf(lm, v[k]);
+                if (nr > 0) rm = fmaxf(rm, w[k]);
+            }
+        }
         lm = block_max(lm, redm);
         rm = block_max(rm, redm);
         if (mv > lm && mv >= rm) out = mi;
     }
-    if (threadIdx.x == 0) cand[tile] = out;
+    if (threadIdx.x == 0) cand[tile] = bad ? TRIG_BAD : out;
 }
 
 // Single block: ordered compaction of the per-tile candidates.
-__global__ __launch_bounds__(1024) void trig_compact_kernel(const int64_t* cand, int64_t n_tiles,
-                                                            const TrigStream* streams, int n_streams,
-                                                            const float* e, TrigRecord* rec,
-                                                            unsigned long long* count) {
+__global__ __launch_bounds__(1024) void trig_compact_kernel(const int64_t* cand, int64_t n_tiles, TrigTable tab,
+                                                            int n_streams, const float* e, TrigHead* head,
+                                                            TrigRecord* rec) {
     __shared__ int wsum[16];
     __shared__ int64_t base_s;
+    const TrigStream* streams = tab.dev ? tab.dev : tab.arg;
     if (threadIdx.x == 0) base_s = 0;
+    bool bad = false;
     __syncthreads();
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int64_t t0 = 0; t0 < n_tiles; t0 += 1024) {
         const int64_t t = t0 + threadIdx.x;
-        const int64_t c = (t < n_tiles) ? cand[t] : -1;
+        const int64_t c = (t < n_tiles) ? cand[t] : TRIG_NONE;
         const int f = c >= 0;
+        bad = bad || c == TRIG_BAD;
         // inclusive scan within the wave
         int x = f;
         for (int off = 1; off < 64; off <<= 1) {
@@ -153,13 +193,8 @@ __global__ __launch_bounds__(1024) void trig_compact_kernel(const int64_t* cand,
         if (threadIdx.x == 0) base_s += total;
         __syncthreads();
     }
-    if (threadIdx.x == 0) *count = (unsigned long long)base_s;
-}
-
-// Clears the trigger count and the non-finite flag (a kernel rather than a memset, so the
-// clearing is an ordinary kernel node for callers that capture the stream).
-__global__ void trig_clear_kernel(unsigned long long* count) {
-    if (threadIdx.x < 2) count[threadIdx.x] = 0ull;
+    bad = __syncthreads_or(bad);
+    if (threadIdx.x == 0) *head = TrigHead{base_s, bad ? 1 : 0};
 }
 
 namespace {
@@ -206,41 +241,48 @@ gwd_status trig_run_on(char* p, const TrigLayout& lay, const std::vector<TrigStr
                        int64_t* n_found, hipStream_t st) {
     TrigStream* d_tab = (TrigStream*)p;
     int64_t* d_cand = (int64_t*)(p + lay.tab_bytes);
-    TrigRecord* d_rec = (TrigRecord*)(p + lay.tab_bytes + lay.cand_bytes);
-    unsigned long long* d_count = (unsigned long long*)(p + lay.tab_bytes + lay.cand_bytes + lay.rec_bytes);
-    int* d_flag = (int*)(d_count + 1);
-    hipError_t err = hipMemcpyAsync(d_tab, tab.data(), n_streams * sizeof(TrigStream), hipMemcpyHostToDevice, st);
-    if (err != hipSuccess) return hip_fail(err, "hipMemcpyAsync(trigger table)");
-    hipLaunchKernelGGL(trig_clear_kernel, dim3(1), dim3(64), 0, st, d_count);
-    err = hipGetLastError();
-    if (err != hipSuccess) return hip_fail(err, "trig_clear_kernel launch");
-    hipLaunchKernelGGL(trig_tile_kernel, dim3((unsigned)n_tiles), dim3(256), 0, st, e, d_tab, n_streams, wc, thr,
-                       d_cand, d_flag);
+    TrigHead* d_head = (TrigHead*)(p + lay.tab_bytes + lay.cand_bytes);
+    TrigRecord* d_rec = (TrigRecord*)(d_head + 1);
+    TrigTable arg{};
+    hipError_t err = hipSuccess;
+    if (n_streams <= TRIG_ARG) {
+        std::copy(tab.begin(), tab.begin() + n_streams, arg.arg);
+    } else {
+        arg.dev = d_tab;
+        err = hipMemcpyAsync(d_tab, tab.data(), n_streams * sizeof(TrigStream), hipMemcpyHostToDevice, st);
+        if (err != hipSuccess) return hip_fail(err, "hipMemcpyAsync(trigger table)");
+    }
+    hipLaunchKernelGGL(trig_tile_kernel, dim3((unsigned)n_tiles), dim3(256), 0, st, e, arg, n_streams, wc, thr, d_cand);
     err = hipGetLastError();
     if (err != hipSuccess) return hip_fail(err, "trig_tile_kernel launch");
-    hipLaunchKernelGGL(trig_compact_kernel, dim3(1), dim3(1024), 0, st, d_cand, n_tiles, d_tab, n_streams, e, d_rec,
-                       d_count);
+    hipLaunchKernelGGL(trig_compact_kernel, dim3(1), dim3(1024), 0, st, d_cand, n_tiles, arg, n_streams, e, d_head, d_rec);
     err = hipGetLastError();
     if (err != hipSuccess) return hip_fail(err, "trig_compact_kernel launch");
-    unsigned long long hc[2] = {0, 0};
-    err = hipMemcpyAsync(hc, d_count, 16, hipMemcpyDeviceToHost, st);
+    static_assert(sizeof(TrigRecord) == sizeof(gwd_trigger), "record layout");
+    struct {
+        TrigHead head;
+        gwd_trigger rec[TRIG_FIRST];
+    } first;
+    const int64_t nfirst = std::min<int64_t>(std::min<int64_t>(n_tiles, TRIG_FIRST), capacity);
+    err = hipMemcpyAsync(&first, d_head, sizeof(TrigHead) + nfirst * sizeof(TrigRecord), hipMemcpyDeviceToHost, st);
     if (err != hipSuccess) return hip_fail(err, "hipMemcpyAsync(count)");
     err = hipStreamSynchronize(st);
     if (err != hipSuccess) return hip_fail(err, "hipStreamSynchronize");
-    const int flag = (int)(hc[1] & 0xffffffffu);
-    if (flag) {
+    if (first.head.bad) {
         set_error("gwd_triggers: non-finite ensemble score");
         return GWD_ERR_NONFINITE;
     }
-    const int64_t cnt = (int64_t)hc[0];
+    const int64_t cnt = first.head.count;
     *n_found = cnt;
     const int64_t ncopy = cnt < capacity ? cnt : capacity;
     if (ncopy > 0) {
-        static_assert(sizeof(TrigRecord) == sizeof(gwd_trigger), "record layout");
-        err = hipMemcpyAsync(out, d_rec, ncopy * sizeof(TrigRecord), hipMemcpyDeviceToHost, st);
-        if (err != hipSuccess) return hip_fail(err, "hipMemcpyAsync(records)");
-        err = hipStreamSynchronize(st);
-        if (err != hipSuccess) return hip_fail(err, "hipStreamSynchronize");
+        std::copy(first.rec, first.rec + std::min(ncopy, nfirst), out);
+        if (ncopy > nfirst) {
+            err = hipMemcpyAsync(out + nfirst, d_rec + nfirst, (ncopy - nfirst) * sizeof(TrigRecord), hipMemcpyDeviceToHost, st);
+            if (err != hipSuccess) return hip_fail(err, "hipMemcpyAsync(records)");
+            err = hipStreamSynchronize(st);
+            if (err != hipSuccess) return hip_fail(err, "hipStreamSynchronize");
+        }
         for (int64_t i = 0; i < ncopy; ++i) out[i].prob = (float)(1.0 / (1.0 + exp(-(double)out[i].logit)));
     }
     if (cnt > capacity) {
