@@ -184,8 +184,8 @@ gwd_status check_forward(const gwd_model* m, const gwd_stream* streams, int32_t 
 // (batch_windows x window, so the workspace is never larger than the request's own windows need);
 // several streams share a batch, with windows of at most an eighth of it, and each window stops at its
 // stream's end (FwdBatch::rows). Scores are bit for bit those of the request's own windows. Windows
-// 4096 / 256, four members in BF16: 8 s of strain 15.1 -> 1.94 ms, 256 s 459 -> 31.3 ms; one FP32
-// member, 16 s: 84.6 -> 6.03 ms.
+// 4096 / 256, four members in BF16: 8 s of strain 15.1 -> 1.94 ms (1.20 ms with the members in one launch),
+// 256 s 459 -> 31.3 ms; one FP32 member, 16 s: 84.6 -> 6.03 ms.
 static bool merged_windows(const gwd_model* m, const gwd_stream* streams, int n_streams, int64_t total_win, int& window,
                            int& stride) {
     const int64_t H = (rf_of(&m->arch) - 1 + 127) / 128 * 128;   // overlap: whole 128-row tiles
@@ -313,7 +313,15 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
     const int64_t stream_bytes = (desc_bytes + first_bytes + row_bytes + 255) & ~255LL;
     const int64_t persist_bytes = persist ? persistent_table_bytes(m, window) : 0;
     const int64_t tab_bytes = std::max<int64_t>(m->ws_tab_bytes, stream_bytes + persist_bytes);
-    int64_t act_bytes = m->arch.kind == 1 ? 3 * (int64_t)nb_max * window * kC * 4 : 0;
+    // as many members per launch as fit a batch of rows: a small request's launches would leave most of
+    // the chip idle, or run each block for one chunk beside a warm-up chunk. Four members: BF16, 8 s
+    // 1.98 -> 1.20 ms, five ragged FP8 streams of 22 s 5.94 -> 2.98 ms, two-branch, 32 s 3.25 -> 2.85 ms;
+    // 256 s (two members per launch) 31.3 ms either way
+    const int64_t rows_batch = (int64_t)nb_max * window;
+    fb.n_group = persist || m->arch.kind != 1
+                     ? 1 : member_group(m, (int)std::max<int64_t>(1, std::min<int64_t>(m->n_members, batch_rows / rows_batch)));
+    fb.act_stride = rows_batch * kC;
+    int64_t act_bytes = m->arch.kind == 1 ? 3 * fb.n_group * fb.act_stride * 4 : 0;
     if (persist) {  // two blocks per compute unit (at most one per window), each holding up to
                     // kPersistWindows of its windows at a time
         int n_cu = 0;
@@ -382,7 +390,8 @@ hipError_t forward_enqueue(gwd_model* m, FwdBatch fb, int64_t total_win, int nb_
         if (e == hipSuccess && after_batch) e = after_batch(ctx, 0, st);
         return e;
     }
-    const int64_t act = m->arch.kind == 1 ? (int64_t)nb_max * fb.T * kC * 4 : 0;
+    const int group = fb.n_group;
+    const int64_t act = m->arch.kind == 1 ? group * fb.act_stride * 4 : 0;
     float* x_a = (float*)(base + tab_bytes);
     float* x_b = (float*)(base + tab_bytes + act);
     float* skip = (float*)(base + tab_bytes + 2 * act);
@@ -396,8 +405,9 @@ hipError_t forward_enqueue(gwd_model* m, FwdBatch fb, int64_t total_win, int nb_
         const auto f1 = std::lower_bound(f0, f.end(), w0 + fb.nb);
         fb.first_idx = f0 - f.begin();
         fb.n_first = (int)(f1 - f0);
-        for (int mem = 0; mem < m->n_members; ++mem) {
+        for (int mem = 0; mem < m->n_members; mem += group) {
             fb.member = mem;
+            fb.n_group = std::min(group, m->n_members - mem);
             hipError_t e = m->arch.kind == 0 ? launch_tiny_forward(m, fb, st)
                                              : launch_wavenet_forward(m, fb, x_a, x_b, skip, st);
             if (e != hipSuccess) return e;

@@ -468,6 +468,12 @@ struct FusedArgs {
     int d0, T;             // dilation of the first layer; window length
     int n_seg, seg_chunks; // segments per sub-sequence, chunks per segment
     const int32_t* win_rows;  // per window of the launch: rows anyone needs (null: all T)
+    // members of the launch, blocks of each, byte offset of each one's weights from the first one's, and
+    // the floats between their activation buffers (x counted in pairs of bf16)
+    // mem_xcds: the XCDs of each member (0: members alternate block by block)
+    int n_mem, mem_blocks, mem_xcds;
+    int64_t mem_off[kMaxGroup];
+    int64_t act_stride;
     const StreamDesc* streams;
     int n_streams;
     int64_t win_base;
@@ -486,6 +492,30 @@ struct FusedArgs {
     int64_t rec_pre_stride;
     uint16_t* rec_x;
     int64_t rec_x_stride;
+};
+
+// The block's member in a launch over several members of the ensemble, and its index among that
+// member's blocks (bid may lie past the last one). Two, four or eight members are dealt to the eight XCDs
+// evenly, so that each L2 holds the weights of one member (six layers of four members, 4.7 MB in bf16,
+// are more than it holds), and a member's blocks alternate over its XCDs, since windows of ragged
+// streams differ in length; other counts alternate block by block.
+struct FusedMember {
+    int mem, bid;
+    int64_t off;
+    __device__ explicit FusedMember(const FusedArgs& p) {
+        const int b = blockIdx.x;
+        if (p.mem_xcds) {
+            const int x = b & 7;
+            mem = x / p.mem_xcds;
+            bid = (b >> 3) * p.mem_xcds + x % p.mem_xcds;
+        } else {
+            mem = b % p.n_mem;
+            bid = b / p.n_mem;
+        }
+        off = p.mem_off[mem];
+    }
+    template <class T>
+    __device__ const T* weights(const T* q) const { return (const T*)((const char*)q + off); }
 };
 
 __device__ inline uint8_t* fu_buf(uint8_t* lds, int j) { return lds + (j == 0 ? FU_B0 : j == 1 ? FU_B1 : FU_B2); }
@@ -560,17 +590,21 @@ struct ChunkRows {
 template <bool FROM_STREAM, bool SKIP_INIT, int NL, bool LAST, bool G2, int DBG = 0>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fused_bf16_kernel(FusedArgs p) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[FU_LDS];
-#define GWD_IO_BID blockIdx.x
-#define GWD_IO_X_IN p.x_in
-#define GWD_IO_X_OUT p.x_out
-#define GWD_IO_SKIP p.skip
+    const FusedMember fm(p);
+    if (fm.bid >= p.mem_blocks) return;
+#define GWD_IO_BID fm.bid
+#define GWD_IO_X_IN (p.x_in + fm.mem * p.act_stride * 2)
+#define GWD_IO_X_OUT (p.x_out + fm.mem * p.act_stride * 2)
+#define GWD_IO_SKIP (p.skip + fm.mem * p.act_stride)
 #define GWD_IO_WIN_BASE p.win_base
+#define GWD_IO_W(q) fm.weights(q)
 #include "fused_bf16_body.inc"
 #undef GWD_IO_BID
 #undef GWD_IO_X_IN
 #undef GWD_IO_X_OUT
 #undef GWD_IO_SKIP
 #undef GWD_IO_WIN_BASE
+#undef GWD_IO_W
 }
 
 // The same body for the persistent forward: one block's piece of a launch on the window it owns.
@@ -581,12 +615,14 @@ __device__ __forceinline__ void fused_bf16_body(const FA& p, const IO& io, uint8
 #define GWD_IO_X_OUT io.x_out()
 #define GWD_IO_SKIP io.skip()
 #define GWD_IO_WIN_BASE io.win_base()
+#define GWD_IO_W(q) (q)
 #include "fused_bf16_body.inc"
 #undef GWD_IO_BID
 #undef GWD_IO_X_IN
 #undef GWD_IO_X_OUT
 #undef GWD_IO_SKIP
 #undef GWD_IO_WIN_BASE
+#undef GWD_IO_W
 }
 
 
@@ -644,17 +680,21 @@ __device__ inline uint32_t bf16x4_to_e4m3(uint2 w) { return bf16x2_to_e4m3(w.x) 
 template <bool FROM_STREAM, bool SKIP_INIT, int NL, bool LAST, bool G2, bool DBG = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fused_fp8_kernel(FusedArgs p) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[FX_LDS];
-#define GWD_IO_BID blockIdx.x
-#define GWD_IO_X_IN p.x_in
-#define GWD_IO_X_OUT p.x_out
-#define GWD_IO_SKIP p.skip
+    const FusedMember fm(p);
+    if (fm.bid >= p.mem_blocks) return;
+#define GWD_IO_BID fm.bid
+#define GWD_IO_X_IN (p.x_in + fm.mem * p.act_stride * 2)
+#define GWD_IO_X_OUT (p.x_out + fm.mem * p.act_stride * 2)
+#define GWD_IO_SKIP (p.skip + fm.mem * p.act_stride)
 #define GWD_IO_WIN_BASE p.win_base
+#define GWD_IO_W(q) fm.weights(q)
 #include "fused_fp8_body.inc"
 #undef GWD_IO_BID
 #undef GWD_IO_X_IN
 #undef GWD_IO_X_OUT
 #undef GWD_IO_SKIP
 #undef GWD_IO_WIN_BASE
+#undef GWD_IO_W
 }
 
 // The same body for the persistent forward: one block's piece of a launch on the window it owns.
@@ -665,12 +705,14 @@ __device__ __forceinline__ void fused_fp8_body(const FA& p, const IO& io, uint8_
 #define GWD_IO_X_OUT io.x_out()
 #define GWD_IO_SKIP io.skip()
 #define GWD_IO_WIN_BASE io.win_base()
+#define GWD_IO_W(q) (q)
 #include "fused_fp8_body.inc"
 #undef GWD_IO_BID
 #undef GWD_IO_X_IN
 #undef GWD_IO_X_OUT
 #undef GWD_IO_SKIP
 #undef GWD_IO_WIN_BASE
+#undef GWD_IO_W
 }
 
 
@@ -692,6 +734,9 @@ static int fused_layers_in(const gwd_model* m, int l, int T, int mode) {
     const int d0 = 1 << i;
     if (i + 4 == lps && T > 0 && (T + d0 - 1) / d0 <= FU_ROWS) return 4;
     return l + 2 < L - 1 ? 3 : 0;
+}
+int member_group(const gwd_model* m, int n) {
+    return m->arch.kind == 1 && fused_layers_in(m, 0, 1, m->lp_fuse) == 6 ? std::min(n, kMaxGroup) : 1;
 }
 static int fused_layers(const gwd_model* m, int l, int T) { return fused_layers_in(m, l, T, m->lp_fuse); }
 // The persistent kernel's grouping: the model's sextets and quads, else triples and quads.
@@ -737,17 +782,18 @@ static hipError_t launch_fused(gwd_model* m, int member, int l, int nl, const ui
     // first costs one warm-up chunk; the autotuner may aim at more blocks (gwd_set_fused_blocks)
     const int64_t per = (int64_t)nb * a.d0;
     const int64_t target = m->fused_blocks > 0 ? m->fused_blocks : 512;
+    const int n_mem = fb ? fb->n_group : 1;
     if (fb && fb->h_rows) {
         // merged windows differ in length: the chunks in use are shared out over the blocks
         a.win_rows = fb->rows + fb->win_base;
         int64_t chunks = 0;
         for (int i = 0; i < nb; ++i) {
             const int64_t sub = (fb->h_rows[fb->win_base + i] + a.d0 - 1) / a.d0;
-            chunks += a.d0 * ((sub + rows - 1) / rows);
+            chunks += a.d0 * ((sub + rows - 1) / rows) * fb->n_group;
         }
         a.seg_chunks = (int)std::min<int64_t>(n_ch, std::max<int64_t>(1, (chunks + target - 1) / target));
     } else {
-        const int want = (int)std::min<int64_t>(n_ch, std::max<int64_t>(1, (target + per - 1) / per));
+        const int want = (int)std::min<int64_t>(n_ch, std::max<int64_t>(1, (target + per * n_mem - 1) / (per * n_mem)));
         a.seg_chunks = (n_ch + want - 1) / want;
     }
     a.n_seg = (n_ch + a.seg_chunks - 1) / a.seg_chunks;
@@ -759,7 +805,13 @@ static hipError_t launch_fused(gwd_model* m, int member, int l, int nl, const ui
         a.win_base = fb->win_base;
         a.S = fb->S;
     }
-    const dim3 grid((unsigned)(per * a.n_seg));
+    a.n_mem = n_mem;
+    a.mem_blocks = (int)(per * a.n_seg);
+    a.act_stride = fb ? fb->act_stride : 0;
+    for (int i = 0; i < n_mem; ++i)
+        a.mem_off[i] = (const char*)m->members[member + i].base - (const char*)m->members[member].base;
+    a.mem_xcds = n_mem > 1 && 8 % n_mem == 0 ? 8 / n_mem : 0;
+    const dim3 grid((unsigned)(a.mem_xcds ? 8 * ((a.mem_blocks + a.mem_xcds - 1) / a.mem_xcds) : a.mem_blocks * n_mem));
     if (dbg && dbg->rec_pre) {  // the training recompute (BF16): per-layer bf16 outputs, no skip sum
         if (FP8 || stream_in || m->two_branch) return hipErrorInvalidValue;
         a.rec_pre = dbg->rec_pre;

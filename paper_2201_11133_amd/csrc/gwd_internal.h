@@ -14,6 +14,8 @@ namespace gwd {
 // Residual / skip / head width of the full-size member; the FP32/BF16/FP8 layer kernels are
 // specialised for it.
 constexpr int kC = 128;
+// Most members of an ensemble that one fused launch takes.
+constexpr int kMaxGroup = 8;
 // Rows (time steps) of one layer-kernel tile.
 constexpr int kBM = 64;
 // Plain member (kind 0, four 16-channel layers and a 1x1 to one logit): per-output-channel weight
@@ -146,6 +148,8 @@ struct FwdBatch {
     int S;              // stride
     int out_mode;
     int member;
+    int n_group;        // members of this launch: member .. member + n_group - 1 (1 but for launches over several)
+    int64_t act_stride; // floats between two members' activation buffers
     int n_members;
     float* out;
     int64_t sum_L;      // total samples (stitched layout)
@@ -159,6 +163,8 @@ struct FwdBatch {
 };
 
 hipError_t launch_tiny_forward(const gwd_model* m, const FwdBatch& fb, hipStream_t st);
+// Members of one launch: up to n of them where every launch of the forward takes several, else 1.
+int member_group(const gwd_model* m, int n);
 hipError_t launch_wavenet_forward(gwd_model* m, const FwdBatch& fb, float* x_a, float* x_b, float* skip,
                                   hipStream_t st);
 hipError_t launch_layer_debug(gwd_model* m, int member, int layer, const float* x_in, int nb, int T,

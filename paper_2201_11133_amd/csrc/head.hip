@@ -22,7 +22,11 @@ __global__ __launch_bounds__(256) void head_kernel(HeadArgs p) {
     int lo, hi;
     owner_rows(p.o, k, sd.length, lo, hi);
     if (t0 + kBM <= lo || t0 >= hi) return;  // uniform over the block
-    head_tile(p, sd, gw, k, t0, lo, hi, p.skip + (gw - p.win_base) * p.o.T * kC, sk, part);
+    // the launch's members in order: the thread that writes a sample's score takes the running minimum
+    for (int mem = 0; mem < p.n_mem; ++mem) {
+        if (mem > 0) __syncthreads();   // the LDS of the member before is read
+        head_tile(p, sd, gw, k, t0, lo, hi, p.skip + mem * p.act_stride + (gw - p.win_base) * p.o.T * kC, sk, part, mem);
+    }
 }
 
 hipError_t wavenet_layers_f32(gwd_model* m, const FwdBatch& fb, float* x_a, float* x_b, float* skip,
@@ -55,8 +59,11 @@ hipError_t launch_wavenet_forward(gwd_model* m, const FwdBatch& fb, float* x_a, 
     if (e != hipSuccess) return e;
     const MemberWeights& mw = m->members[fb.member];
     const float* base = (const float*)mw.base;
-    HeadArgs h;
+    HeadArgs h{};
     h.skip = skip;
+    h.n_mem = fb.n_group;
+    h.act_stride = fb.act_stride;
+    for (int i = 0; i < fb.n_group; ++i) h.mem_off[i] = (const char*)m->members[fb.member + i].base - (const char*)mw.base;
     h.h1w = base + mw.h1w;
     h.h1b = base + mw.h1b;
     h.h2w = base + mw.h2w;

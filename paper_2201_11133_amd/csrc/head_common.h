@@ -13,6 +13,9 @@ struct HeadArgs {
     const float* h1b;
     const float* h2w;
     const float* h2b;
+    int n_mem;             // members of this launch, in order: byte offset of each one's weights from the
+    int64_t mem_off[kMaxGroup];  // first one's, and the floats between their skip sums
+    int64_t act_stride;
     int mid_relu;
     int tile_first;        // first 64-row tile launched per window
     int tiles;             // tiles launched per window
@@ -36,7 +39,10 @@ constexpr int kHS = kC + 4;  // LDS row stride of the skip tile (floats): 16-byt
 // from LDS. Epilogue per lane: bias, activation and the dot with w_h2 over its 16 hidden units, then
 // the two half-waves and the four waves are added in a fixed order.
 __device__ __forceinline__ void head_tile(const HeadArgs& p, const StreamDesc& sd, int64_t gw, int64_t k, int t0,
-                                          int lo, int hi, const float* skip_rows, float* sk, float (*part)[kBM]) {
+                                          int lo, int hi, const float* skip_rows, float* sk, float (*part)[kBM],
+                                          int mem = 0) {
+    const int64_t off = mem ? p.mem_off[mem] : 0;
+    const auto weights = [&](const float* q) { return (const float*)((const char*)q + off); };
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const float4* src = (const float4*)(skip_rows + (int64_t)t0 * kC);
 #pragma unroll
@@ -49,15 +55,15 @@ __device__ __forceinline__ void head_tile(const HeadArgs& p, const StreamDesc& s
     const int r = lane & 31, hw = lane >> 5;
     const int hid0 = 32 * wv;
     float4 a[16];
-    const float4* wrow = (const float4*)(p.h1w + (int64_t)(hid0 + r) * kC) + hw;
+    const float4* wrow = (const float4*)(weights(p.h1w) + (int64_t)(hid0 + r) * kC) + hw;
 #pragma unroll
     for (int g = 0; g < 16; ++g) a[g] = wrow[2 * g];
     float bias[16], w2[16];
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
         const int m = hid0 + 8 * (i >> 2) + 4 * hw + (i & 3);
-        bias[i] = p.h1b[m];
-        w2[i] = p.h2w[m];
+        bias[i] = weights(p.h1b)[m];
+        w2[i] = weights(p.h2w)[m];
     }
     __syncthreads();
 #pragma unroll
@@ -86,8 +92,10 @@ __device__ __forceinline__ void head_tile(const HeadArgs& p, const StreamDesc& s
     if (tid < kBM) {
         const int t = t0 + tid;
         if (t >= lo && t < hi) {
-            const float z = ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid])) + p.h2b[0];
-            emit_logit(p.o, sd, gw, k, t, z);
+            const float z = ((part[0][tid] + part[1][tid]) + (part[2][tid] + part[3][tid])) + weights(p.h2b)[0];
+            OutDesc o = p.o;
+            o.member += mem;
+            emit_logit(o, sd, gw, k, t, z);
         }
     }
 }

@@ -46,3 +46,25 @@ def test_merged_windows_give_the_same_scores(g, prec, two):
                         plan.close()
     assert g.lib.gwd_set_window_merging(m.h, 2) == g.ERR_ARG and g.lib.gwd_set_window_merging(None, 1) == g.ERR_ARG
     m.close()
+
+
+@pytest.mark.parametrize("prec,members", [("bf16", 3), ("bf16", 4), ("bf16", 9), ("fp8", 5), ("fp8", 8)])
+def test_members_of_one_launch(g, prec, members):
+    """Launches over several members (all counts that divide the XCDs and some that do not, more members
+    than one launch takes): each member's scores equal those of a model of its own, bit for bit, and the
+    ensemble score is their minimum."""
+    from paper_2201_11133_amd import synth
+    print(f"case: {prec} {members} members", flush=True)
+    blobs = np.stack([synth.full_weights(60 + i) for i in range(members)])
+    xs = [to_dev(synth.make_stream(600 + i, L / 4096, 0)[0][:L]) for i, L in enumerate((40000, 64, 9001))]
+    n = sum(len(x) for x in xs)
+    m = g.Model(g.full_arch(), blobs, prec)
+    e = m.forward(xs, 4096, 256, 1).clone()
+    w = m.forward(xs[:1], 4096, 1024, 2).clone().reshape(members, -1)
+    m.close()
+    for i in range(members):
+        one = g.Model(g.full_arch(), blobs[i], prec)
+        assert torch.equal(e[n * (1 + i): n * (2 + i)], one.forward(xs, 4096, 256, 0))
+        assert torch.equal(w[i], one.forward(xs[:1], 4096, 1024, 2))
+        one.close()
+    assert torch.equal(e[:n], e[n:].reshape(members, n).min(dim=0).values)
