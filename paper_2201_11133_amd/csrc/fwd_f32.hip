@@ -3,12 +3,18 @@
 // Gated residual layer ("AI architecture", Fig. 1: a modified WaveNet; one gated layer is
 //   pre = W0 x[t-d] + W1 x[t] + b, g = tanh(pre[:C]) * sigmoid(pre[C:]),
 //   skip += W_s g + b_s, x += W_r g + b_r)
-// as two chained GEMMs per tile of 64 time steps of one window:
-//   phase 1  [64 x 256] = A [64 x 256] * Bc [256 x 256],  A[t] = [x[t-d] | x[t]] staged in LDS
+// as two chained GEMMs per tile of 32 time steps of one window:
+//   phase 1  [32 x 256] = A [32 x 256] * Bc [256 x 256],  A[t] = [x[t-d] | x[t]] staged in LDS
 //   gate     in registers; g written over the x[t-d] half of the LDS tile
-//   phase 2  [64 x 256] = g [64 x 128] * Brs [128 x 256]  (res | skip), epilogue updates x and skip
+//   phase 2  [32 x 256] = g [32 x 128] * Brs [128 x 256]  (res | skip), epilogue updates x and skip
 // Wave w of the 4 owns output columns [32w, 32w+32) and [128+32w, 128+32w+32), so the filter and
 // gate halves of one channel meet in the same lane and the gate needs no data exchange.
+//
+// The matrix cores bound it (phase 1 at the fp64 rate of 67 TFLOP/s, phase 2 at 154 TFLOP/s in fp32: 0.31 ms of
+// 131,072 rows). Staging, gate and epilogue of one block hide behind the products of the others on its CU:
+// tiles of 32 rows leave room for four blocks per CU (126 VGPRs, 33 KB of LDS) where 64 rows leave two, and give
+// small batches twice the blocks, for twice the weight reads from L2. 30 layers with 64 | 32 rows per tile:
+// 4,096 rows 1.71 | 0.96 ms, 16,384 rows 1.77 | 1.58 ms, 131,072 rows 11.5 | 10.6 ms.
 //
 // Accuracy: operands and stored activations are fp32. Phase 1 (K = 256) accumulates in fp64 on
 // v_mfma_f64_16x16x4f64 (fp32 operands convert exactly): with fp32 accumulation over K = 256 the
@@ -23,6 +29,9 @@ namespace gwd {
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
+constexpr int TM = 32;       // time steps per block
+constexpr int RB = TM / 16;  // 16-row blocks of phase 1
+constexpr int R2 = TM / 32;  // 32-row blocks of phase 2
 constexpr int LDA = 2 * kC + 4;  // padded LDS row (floats): 16-byte aligned rows, staggered banks
 #ifndef GWD_FOLD
 #define GWD_FOLD 4
@@ -78,21 +87,21 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 __device__ inline float f4get(const float4& v, int i) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
 
 template <bool FROM_STREAM, bool SKIP_INIT, bool LAST>
-__global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
-    __shared__ __attribute__((aligned(16))) float A[kBM * LDA];
+__global__ __launch_bounds__(256, 4) void layer_f32_kernel(LayerArgsF32 p) {
+    __shared__ __attribute__((aligned(16))) float A[TM * LDA];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = lane >> 5, r = lane & 31;
     const int tile = xcd_remap(blockIdx.x, gridDim.x);
     const int b = tile / p.tiles_per_window;
-    const int t0 = (tile - b * p.tiles_per_window) * kBM;
+    const int t0 = (tile - b * p.tiles_per_window) * TM;
     if (p.win_rows && t0 >= p.win_rows[b]) return;  // uniform over the block
     const int64_t row0 = (int64_t)b * p.T + t0;
 
-    // ---- stage A = [x[t-d] | x[t]], t in [t0, t0 + 64); x[tau < 0] = 0 (zero window context)
+    // ---- stage A = [x[t-d] | x[t]], t in [t0, t0 + TM); x[tau < 0] = 0 (zero window context)
     if (FROM_STREAM) {
         const int64_t gw = p.win_base + b;
         const StreamDesc sd = p.streams[find_stream(p.streams, p.n_streams, gw)];
         const int64_t start = (gw - sd.win_begin) * p.S;
-        for (int idx = tid; idx < kBM * 64; idx += 256) {
+        for (int idx = tid; idx < TM * 64; idx += 256) {
             const int rr = idx >> 6, q = idx & 63, tap = q >> 5, c = 4 * (q & 31);
             const int t = t0 + rr - (tap == 0 ? p.d : 0);
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -111,7 +120,7 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
             *(float4*)&A[rr * LDA + tap * kC + c] = v;
         }
     } else {
-        for (int idx = tid; idx < kBM * 64; idx += 256) {
+        for (int idx = tid; idx < TM * 64; idx += 256) {
             const int rr = idx >> 6, q = idx & 63, tap = q >> 5, c = 4 * (q & 31);
             const int t = t0 + rr - (tap == 0 ? p.d : 0);
             float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -126,9 +135,9 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
     // the matching gate columns 128 + 32 w + 16 c + [0,16). Step i of group j uses
     // k = 16 j + 4 q + i, so A and B fragments are float4 loads.
     const int q = lane >> 4, r16 = lane & 15;
-    doublex4 acc[4][2][2];
+    doublex4 acc[RB][2][2];
 #pragma unroll
-    for (int rb = 0; rb < 4; ++rb)
+    for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int c = 0; c < 2; ++c) acc[rb][c][0] = acc[rb][c][1] = doublex4{0.0, 0.0, 0.0, 0.0};
     {
@@ -148,15 +157,15 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
                 ng0 = Bg0[(j + 1) * 64];
                 ng1 = Bg1[(j + 1) * 64];
             }
-            float4 a[4];
+            float4 a[RB];
 #pragma unroll
-            for (int rb = 0; rb < 4; ++rb) a[rb] = *(const float4*)(Ab + rb * 16 * LDA + 16 * j);
+            for (int rb = 0; rb < RB; ++rb) a[rb] = *(const float4*)(Ab + rb * 16 * LDA + 16 * j);
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const double bf0 = (double)f4get(f0, i), bf1 = (double)f4get(f1, i);
                 const double bg0 = (double)f4get(g0, i), bg1 = (double)f4get(g1, i);
 #pragma unroll
-                for (int rb = 0; rb < 4; ++rb) {
+                for (int rb = 0; rb < RB; ++rb) {
                     const double av = (double)f4get(a[rb], i);
                     acc[rb][0][0] = MFMA64(av, bf0, acc[rb][0][0]);
                     acc[rb][1][0] = MFMA64(av, bf1, acc[rb][1][0]);
@@ -174,7 +183,7 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
         const int n = 32 * wave + 16 * c + r16;
         const double bf = p.bc[n], bg = p.bc[kC + n];
 #pragma unroll
-        for (int rb = 0; rb < 4; ++rb)
+        for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int m = 16 * rb + q + 4 * i;  // f64 16x16 result: lane 16 q + r, register i -> row q + 4 i
@@ -191,12 +200,15 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
     __syncthreads();
 
     // ---- phase 2: [res | skip] = g Brs, K = 128 in 16 k-groups of 8
-    Tot16 s00, s01, s10, s11;
-    s00.zero(); s01.zero(); s10.zero(); s11.zero();
+    Tot16 sr[R2], ss[R2];         // res (LAST: skip) and skip totals
+#pragma unroll
+    for (int rb = 0; rb < R2; ++rb) {
+        sr[rb].zero();
+        ss[rb].zero();
+    }
     {
-        floatx16 c00 = {}, c01 = {}, c10 = {}, c11 = {};
+        floatx16 cr[R2] = {}, cs[R2] = {};
         const float* A0 = &A[r * LDA + 4 * h];
-        const float* A1 = &A[(32 + r) * LDA + 4 * h];
         const float4* B0 = p.wrs + (size_t)(wave * 16) * 64 + lane;
         const float4* B1 = p.wrs + (size_t)((wave + 4) * 16) * 64 + lane;
         float4 nb0 = B0[0], nb1 = LAST ? nb0 : B1[0];
@@ -207,24 +219,28 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
                 nb0 = B0[(j + 1) * 64];
                 if (!LAST) nb1 = B1[(j + 1) * 64];
             }
-            const float4 a0 = *(const float4*)(A0 + 8 * j);
-            const float4 a1 = *(const float4*)(A1 + 8 * j);
-            c00 = MFMA32(a0.x, b0.x, c00); c10 = MFMA32(a1.x, b0.x, c10);
-            c00 = MFMA32(a0.y, b0.y, c00); c10 = MFMA32(a1.y, b0.y, c10);
-            c00 = MFMA32(a0.z, b0.z, c00); c10 = MFMA32(a1.z, b0.z, c10);
-            c00 = MFMA32(a0.w, b0.w, c00); c10 = MFMA32(a1.w, b0.w, c10);
+            float4 a[R2];
+#pragma unroll
+            for (int rb = 0; rb < R2; ++rb) a[rb] = *(const float4*)(A0 + rb * 32 * LDA + 8 * j);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int rb = 0; rb < R2; ++rb) cr[rb] = MFMA32(f4get(a[rb], i), f4get(b0, i), cr[rb]);
             if (!LAST) {
-                c01 = MFMA32(a0.x, b1.x, c01); c11 = MFMA32(a1.x, b1.x, c11);
-                c01 = MFMA32(a0.y, b1.y, c01); c11 = MFMA32(a1.y, b1.y, c11);
-                c01 = MFMA32(a0.z, b1.z, c01); c11 = MFMA32(a1.z, b1.z, c11);
-                c01 = MFMA32(a0.w, b1.w, c01); c11 = MFMA32(a1.w, b1.w, c11);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int rb = 0; rb < R2; ++rb) cs[rb] = MFMA32(f4get(a[rb], i), f4get(b1, i), cs[rb]);
             }
             if ((j % FOLD) == FOLD - 1) {
-                s00.add(c00); s10.add(c10);
-                c00 = floatx16{}; c10 = floatx16{};
-                if (!LAST) {
-                    s01.add(c01); s11.add(c11);
-                    c01 = floatx16{}; c11 = floatx16{};
+#pragma unroll
+                for (int rb = 0; rb < R2; ++rb) {
+                    sr[rb].add(cr[rb]);
+                    cr[rb] = floatx16{};
+                    if (!LAST) {
+                        ss[rb].add(cs[rb]);
+                        cs[rb] = floatx16{};
+                    }
                 }
             }
         }
@@ -239,10 +255,10 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
             for (int i = 0; i < 16; ++i) {
                 const int m0 = 8 * (i >> 2) + 4 * h + (i & 3);
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb) {
+                for (int rb = 0; rb < R2; ++rb) {
                     const int m = m0 + 32 * rb;
-                    const float rv = (rb ? s10[i] : s00[i]) + br;
-                    const float sv = (rb ? s11[i] : s01[i]) + bs;
+                    const float rv = sr[rb][i] + br;
+                    const float sv = ss[rb][i] + bs;
                     const int64_t o = (row0 + m) * kC + n;
                     p.x_out[o] = A[m * LDA + kC + n] + rv;
                     p.skip[o] = SKIP_INIT ? sv : p.skip[o] + sv;
@@ -254,9 +270,9 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
             for (int i = 0; i < 16; ++i) {
                 const int m0 = 8 * (i >> 2) + 4 * h + (i & 3);
 #pragma unroll
-                for (int rb = 0; rb < 2; ++rb) {
+                for (int rb = 0; rb < R2; ++rb) {
                     const int m = m0 + 32 * rb;
-                    const float sv = (rb ? s10[i] : s00[i]) + bs;
+                    const float sv = sr[rb][i] + bs;
                     const int64_t o = (row0 + m) * kC + n;
                     p.skip[o] = SKIP_INIT ? sv : p.skip[o] + sv;
                 }
@@ -266,8 +282,9 @@ __global__ __launch_bounds__(256, 2) void layer_f32_kernel(LayerArgsF32 p) {
 }
 
 template <bool A_, bool B_, bool C_>
-static hipError_t launch_layer_f32(const LayerArgsF32& a, int nblocks, hipStream_t st) {
-    hipLaunchKernelGGL((layer_f32_kernel<A_, B_, C_>), dim3(nblocks), dim3(256), 0, st, a);
+static hipError_t launch_layer_f32(LayerArgsF32 a, int nb, hipStream_t st) {
+    a.tiles_per_window = a.T / TM;
+    hipLaunchKernelGGL((layer_f32_kernel<A_, B_, C_>), dim3((unsigned)nb * a.tiles_per_window), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -289,8 +306,6 @@ static LayerArgsF32 layer_args(gwd_model* m, int member, int l) {
 hipError_t wavenet_layers_f32(gwd_model* m, const FwdBatch& fb, float* x_a, float* x_b, float* skip,
                               hipStream_t st) {
     const int L = m->arch.n_stacks * m->arch.layers_per_stack;
-    const int tpw = fb.T / kBM;
-    const int nblocks = fb.nb * tpw;
     float* xin = x_a;
     float* xout = x_b;
     for (int l = 0; l < L; ++l) {
@@ -300,16 +315,15 @@ hipError_t wavenet_layers_f32(gwd_model* m, const FwdBatch& fb, float* x_a, floa
         a.skip = skip;
         a.pre_out = nullptr;
         a.T = fb.T;
-        a.tiles_per_window = tpw;
         a.win_rows = fb.rows ? fb.rows + fb.win_base : nullptr;
         a.streams = fb.streams;
         a.n_streams = fb.n_streams;
         a.win_base = fb.win_base;
         a.S = fb.S;
         hipError_t e;
-        if (l == 0) e = launch_layer_f32<true, true, false>(a, nblocks, st);
-        else if (l < L - 1) e = launch_layer_f32<false, false, false>(a, nblocks, st);
-        else e = launch_layer_f32<false, false, true>(a, nblocks, st);
+        if (l == 0) e = launch_layer_f32<true, true, false>(a, fb.nb, st);
+        else if (l < L - 1) e = launch_layer_f32<false, false, false>(a, fb.nb, st);
+        else e = launch_layer_f32<false, false, true>(a, fb.nb, st);
         if (e != hipSuccess) return e;
         float* t = xin; xin = xout; xout = t;
     }
@@ -325,8 +339,7 @@ hipError_t layer_production_f32(gwd_model* m, int member, int l, void* x_in, voi
     a.skip = skip;
     a.pre_out = nullptr;
     a.T = T;
-    a.tiles_per_window = T / kBM;
-    return launch_layer_f32<false, false, false>(a, nb * (T / kBM), st);
+    return launch_layer_f32<false, false, false>(a, nb, st);
 }
 
 hipError_t layer_debug_f32(gwd_model* m, int member, int l, const float* x_in, int nb, int T, float* pre_out,
@@ -338,12 +351,10 @@ hipError_t layer_debug_f32(gwd_model* m, int member, int l, const float* x_in, i
     a.skip = skip;
     a.pre_out = pre_out;
     a.T = T;
-    a.tiles_per_window = T / kBM;
-    const int nblocks = nb * (T / kBM);
-    if (l == 0) return (L == 1) ? launch_layer_f32<false, true, true>(a, nblocks, st)
-                                : launch_layer_f32<false, true, false>(a, nblocks, st);
-    if (l < L - 1) return launch_layer_f32<false, false, false>(a, nblocks, st);
-    return launch_layer_f32<false, false, true>(a, nblocks, st);
+    if (l == 0) return (L == 1) ? launch_layer_f32<false, true, true>(a, nb, st)
+                                : launch_layer_f32<false, true, false>(a, nb, st);
+    if (l < L - 1) return launch_layer_f32<false, false, false>(a, nb, st);
+    return launch_layer_f32<false, false, true>(a, nb, st);
 }
 
 }  // namespace gwd

@@ -13,6 +13,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <vector>
 
 #include "train_internal.h"
@@ -65,7 +66,7 @@ static gwd_status fwd_train_kind1(gwd_model* m, int member, const float* u, int 
     const int LPS = m->arch.layers_per_stack;
     BlobOffsets v = blob_offsets(m->arch);
     const float* w = (const float*)m->canon[member];
-    gwd_status s = ensure_tws(m, 4 * M * kC * 4, st);
+    gwd_status s = ensure_tws(m, (4 * M * kC + kC * kC) * 4, st);
     if (s != GWD_OK) return s;
     float* xa = fptr(m->tws.base, 0);
     float* xb = fptr(m->tws.base, M * kC);
@@ -115,6 +116,7 @@ static gwd_status fwd_train_kind1(gwd_model* m, int member, const float* u, int 
     g.A[0] = APart{R, kC, 0, kC};
     g.B[0] = BPart{w + v.h1w, 1, kC};  // B(k = c, n = j) = h1.W[j][c]
     g.nparts = 1; g.M = M; g.N = kC; g.T = T; g.C = H; g.ldc = kC; g.bias = w + v.h1b;
+    g.btf = fptr(m->tws.base, 4 * M * kC);
     e = gemm_rows(g, st);
     if (e != hipSuccess) return hip_fail(e, "head gemm");
     e = launch_head_logit(H, M, w + v.h2w, w + v.h2b, m->arch.head_mid_relu, logits, st);
@@ -130,8 +132,9 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
     const int mid = m->arch.head_mid_relu;
     BlobOffsets v = blob_offsets(m->arch);
     const float* w = (const float*)m->canon[member];
-    const int64_t RPC = T;   // weight-gradient rows per chunk: one window
-    const int64_t nch = (M + RPC - 1) / RPC;
+    // weight-gradient partials: one chunk per window, or split windows (gemm_wgrad: at most 1,023 output
+    // tiles of 128 x 128 then, the 256 products of 2C x 2C this leaves room for)
+    const int64_t nch = std::max<int64_t>(B, 256);
     // workspace (floats): XS[LPS][M][128] PRE[LPS][M][256] G DG DX DSKIP SKS R H DH AH [M][128] each, partials
     const int64_t f_xs = 0, f_pre = f_xs + (int64_t)LPS * M * kC, f_g = f_pre + (int64_t)LPS * M * 2 * kC;
     const int64_t f_dg = f_g + M * kC, f_dx = f_dg + M * kC, f_ds = f_dx + M * kC, f_sks = f_ds + M * kC;
@@ -140,7 +143,7 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
     // partials of the largest weight-gradient product (2C x 2C per chunk), then the group sums of
     // its two-stage reduction (at most 64 groups)
     const int64_t f_cpart = f_part + (nch + 64) * 2 * kC * 2 * kC;   // column sums fused into them
-    const int64_t total = f_cpart + (nch + 64) * 2 * kC;
+    const int64_t total = f_cpart + (4 * nch + 64) * 2 * kC;
     gwd_status s = ensure_tws(m, total * 4, st);
     if (s != GWD_OK) return s;
     void* b = m->tws.base;
@@ -164,7 +167,7 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
         g.A[0] = APart{R, kC, 0, kC};
         g.B[0] = BPart{w + v.h1w, 1, kC};
         g.nparts = 1; g.M = M; g.N = kC; g.T = T; g.C = H; g.ldc = kC; g.bias = w + v.h1b;
-        g.bt = BT;
+        g.bt = BT; g.btf = fptr(b, f_bt);
         HIPCHK(gemm_rows(g, st), "head gemm");
     }
     HIPCHK(launch_head_bwd_elem(H, dz, M, w + v.h2w, mid, DH, AH, st), "head bwd");
@@ -173,7 +176,7 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
     {
         WgradArgs a{};
         a.A[0] = APart{DH, kC, 0, kC}; a.nparts = 1; a.Ktot = kC;
-        a.B = R; a.ldb = kC; a.N = kC; a.M = M; a.T = T; a.rows_per_chunk = RPC; a.part = PART; a.part_capacity = PART_CAP; a.bf16 = BT != nullptr;
+        a.B = R; a.ldb = kC; a.N = kC; a.M = M; a.T = T; a.part = PART; a.part_capacity = PART_CAP; a.bf16 = BT != nullptr;
         a.cpart = CPART; a.cpart_capacity = CPART_CAP;
         const WgradDst cd{grad + v.h1b, nullptr, kC, 1, false};
         HIPCHK(gemm_wgrad(a, WgradDst{grad + v.h1w, nullptr, (int64_t)kC * kC, 1, false}, st, &cd), "d h1.W, d h1.b");
@@ -183,7 +186,7 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
         g.A[0] = APart{DH, kC, 0, kC};
         g.B[0] = BPart{w + v.h1w, kC, 1};      // B(k = j, n = c) = h1.W[j][c]
         g.nparts = 1; g.M = M; g.N = kC; g.T = T; g.C = DS; g.ldc = kC; g.mask = skip; g.ldm = kC;
-        g.bt = BT;
+        g.bt = BT; g.btf = fptr(b, f_bt);
         HIPCHK(gemm_rows(g, st), "dskip");
     }
     HIPCHK(launch_fill(DX, M * kC, 0.f, st), "zero dx");
@@ -249,17 +252,18 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
                 g.nparts = 2;
             }
             g.M = M; g.N = kC; g.T = T; g.C = DG; g.ldc = kC;
-            g.bt = BT;
-            // BF16/FP8 members: g and dpre in bf16 (the GEMMs that read them round to bf16 anyway),
-            // formed in the dg GEMM's epilogue (dg itself is stored only when captured)
+            g.bt = BT; g.btf = fptr(b, f_bt);
+            // g and dpre are formed in the dg GEMM's epilogue (dg itself is stored only when captured);
+            // BF16/FP8 members: in bf16 (the GEMMs that read them round to bf16 anyway)
             uint16_t* G16 = BT ? (uint16_t*)G : nullptr;
             uint16_t* DPRE16 = BT ? (uint16_t*)DPRE : nullptr;
             if (BT) {
                 g.gpre = (const uint16_t*)pre; g.g16 = G16; g.dpre16 = DPRE16;
-                if (!cap) g.C = nullptr;
+            } else {
+                g.gpre32 = pre; g.g32 = G; g.dpre32 = DPRE;
             }
+            if (!cap) g.C = nullptr;
             HIPCHK(gemm_rows(g, st), "dg");
-            if (!BT) HIPCHK(launch_gate_bwd(pre, DG, M, G, DPRE, st), "gate bwd");
             if (cap) {
                 HIPCHK(capture(cap[4], DG, M * kC, false, st), "capture dg");
                 HIPCHK(capture(cap[5], BT ? (const void*)G16 : G, M * kC, BT != nullptr, st), "capture g");
@@ -274,7 +278,7 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
                     a.A[1] = APart{DX, kC, 0, kC};
                     a.nparts = 2; a.Ktot = 2 * kC;
                 }
-                a.B = G; a.ldb = kC; a.N = kC; a.M = M; a.T = T; a.rows_per_chunk = RPC; a.part = PART; a.part_capacity = PART_CAP; a.bf16 = BT != nullptr;
+                a.B = G; a.ldb = kC; a.N = kC; a.M = M; a.T = T; a.part = PART; a.part_capacity = PART_CAP; a.bf16 = BT != nullptr;
                 a.B16 = G16;
                 // with the residual bias gradient (column sums of dx'; those of the bf16 dskip operand
                 // are dropped)
@@ -296,21 +300,14 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
             {
                 WgradArgs a{};
                 a.A[0] = APart{DPRE, 2 * kC, 0, 2 * kC, DPRE16}; a.nparts = 1; a.Ktot = 2 * kC;
-                a.B = xs_i; a.ldb = kC; a.N = kC; a.M = M; a.T = T; a.rows_per_chunk = RPC; a.part = PART; a.part_capacity = PART_CAP; a.bf16 = BT != nullptr;
-                a.bshift = 0;
-                if (BT) {  // both taps in one product: B = [x(t) | x(t - d)] stacked along n, dpre read once,
-                           // with the bias gradient (column sums of dpre)
-                    a.B16 = (const uint16_t*)xs_i;
-                    a.N = 2 * kC; a.nbparts = 2; a.bshift1 = -d;
-                    a.cpart = CPART; a.cpart_capacity = CPART_CAP;
-                    const WgradDst cd{grad + v.dil_b[l], nullptr, 2 * kC, 1, false};
-                    HIPCHK(gemm_wgrad(a, WgradDst{grad + v.dil_w[l], nullptr, 0, 1, true}, st, &cd), "d dil");
-                } else {
-                    HIPCHK(gemm_wgrad(a, grad + v.dil_w[l] + 1, 2, st), "d dil.W tap1");
-                    a.bshift = -d;
-                    HIPCHK(gemm_wgrad(a, grad + v.dil_w[l], 2, st), "d dil.W tap0");
-                    HIPCHK(colsum(DPRE, 2 * kC, M, 2 * kC, nullptr, 0, 0, PART, PART_CAP, grad + v.dil_b[l], 1, st), "d dil.b");
-                }
+                a.B = xs_i; a.ldb = kC; a.N = kC; a.M = M; a.T = T; a.part = PART; a.part_capacity = PART_CAP; a.bf16 = BT != nullptr;
+                // both taps in one product: B = [x(t) | x(t - d)] stacked along n, dpre read once, with
+                // the bias gradient (column sums of dpre)
+                if (BT) a.B16 = (const uint16_t*)xs_i;
+                a.N = 2 * kC; a.nbparts = 2; a.bshift1 = -d;
+                a.cpart = CPART; a.cpart_capacity = CPART_CAP;
+                const WgradDst cd{grad + v.dil_b[l], nullptr, 2 * kC, 1, false};
+                HIPCHK(gemm_wgrad(a, WgradDst{grad + v.dil_w[l], nullptr, 0, 1, true}, st, &cd), "d dil");
             }
             // dx = dx' + dpre[t] W1 + dpre[t+d] W0   (W_tap as [n][c]: dil.W[(n C + c) 2 + tap])
             {
@@ -320,7 +317,7 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
                 g2.A[1] = APart{DPRE, 2 * kC, d, 2 * kC, DPRE16};
                 g2.B[1] = BPart{w + v.dil_w[l], 2 * kC, 2};
                 g2.nparts = 2; g2.M = M; g2.N = kC; g2.T = T; g2.C = DX; g2.ldc = kC; g2.beta = 1.f;
-                g2.bt = BT;
+                g2.bt = BT; g2.btf = fptr(b, f_bt);
                 HIPCHK(gemm_rows(g2, st), "dx");
             }
             if (cap) HIPCHK(capture(cap[7], DX, M * kC, false, st), "capture dx_out");

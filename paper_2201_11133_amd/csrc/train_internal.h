@@ -39,6 +39,11 @@ struct GemmRowsArgs {
     const uint16_t* gpre;
     uint16_t* g16;
     uint16_t* dpre16;
+    float* btf;          // scratch of the fp32 form (N x sum K floats)
+    // the gate-backward epilogue in fp32: pre-activations gpre32 [M][256], g32 [M][128], dpre32 [M][256]
+    const float* gpre32;
+    float* g32;
+    float* dpre32;
 };
 
 struct WgradArgs {
@@ -51,12 +56,12 @@ struct WgradArgs {
     int N;
     int64_t M;
     int T;
-    int64_t rows_per_chunk;
+    int64_t rows_per_chunk;  // (set by gemm_wgrad)
     float* part;  // [nchunks][Ktot][N]
     int64_t part_capacity;  // floats available at part (partials, then the reduction's scratch)
     bool bf16 = false;      // operands rounded to bf16 (fp32 accumulation): BF16/FP8 members
     const uint16_t* B16 = nullptr;  // with bf16: B already in bf16 (same layout as B, which is unused)
-    // B parts stacked along n (bf16 operands only): N / nbparts columns each, all from the same B
+    // B parts stacked along n: N / nbparts columns each, all from the same B
     // rows, part 0 shifted by bshift and part 1 by bshift1
     int nbparts = 1;
     int bshift1 = 0;
@@ -81,20 +86,14 @@ struct WgradDst {
 };
 
 hipError_t gemm_rows(const GemmRowsArgs& a, hipStream_t st);
-// dst (+)= reduced partials: out_mode 0 row-major [K][N]; 2: element (k, n) at dst[(k N + n) * 2]
-// (one tap of a conv weight [n_out][c][2])
-hipError_t gemm_wgrad(const WgradArgs& a, float* dst, int out_mode, hipStream_t st);
 // With a.cpart set, cdst receives the column sums of A (element k of the Ktot sums, mapped like dst).
 hipError_t gemm_wgrad(const WgradArgs& a, const WgradDst& dst, hipStream_t st, const WgradDst* cdst = nullptr);
-// dst[n * dst_stride] += sum_rows f(X[row][n]) * w[row * wstride]   (w optional, f = id or ReLU)
+// dst[n * dst_stride] += sum_rows f(X[row][n]) * w[row * wstride]   (w optional, f = id or ReLU; N = 4 c and
+// aligned rows, or one column without w and f)
 hipError_t colsum(const float* X, int64_t ldx, int64_t M, int N, const float* w, int64_t wstride, int relu,
                   float* part, int64_t part_capacity, float* dst, int64_t dst_stride, hipStream_t st);
 hipError_t launch_input_proj(const float* u, int64_t M, const float* w_in, const float* b_in, float* x0,
                              hipStream_t st);
-hipError_t launch_gate_bwd(const float* pre, const float* dg, int64_t M, float* g, float* dpre, hipStream_t st);
-// dst[n * dst_stride] += sum_rows X[row][n] for bf16 X (N % 4 == 0, N <= 1024, ldx % 4 == 0)
-hipError_t colsum16(const uint16_t* X, int64_t ldx, int64_t M, int N, float* part, int64_t part_capacity, float* dst,
-                    int64_t dst_stride, hipStream_t st);
 hipError_t launch_head_bwd_elem(const float* h, const float* dz, int64_t M, const float* w2, int mid, float* dh,
                                 float* ah, hipStream_t st);
 hipError_t launch_head_logit(const float* h, int64_t M, const float* w2, const float* b2, int mid, float* z,

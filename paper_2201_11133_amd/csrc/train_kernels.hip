@@ -13,78 +13,8 @@ namespace gwd {
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 #define MFMA32(a, b, c) __builtin_amdgcn_mfma_f32_32x32x2f32((a), (b), (c), 0, 0, 0)
 
-constexpr int GT = 64;   // output tile (rows x columns)
-constexpr int GK = 32;   // k chunk staged in LDS
-
-__device__ inline float part_a(const APart& p, int64_t row, int T, int k) {
-    const int64_t b = row / T;
-    const int t = (int)(row - b * T) + p.shift;
-    if (t < 0 || t >= T) return 0.f;
-    return p.ptr[(b * T + t) * p.ld + k];
-}
-
-// Source row of operand part p for output row `row`, or -1 when the shifted time step leaves its
-// window (zero operand): one division per row, done once.
-__device__ inline int64_t part_row(const APart& p, int64_t row, int T) {
-    const int64_t b = row / T;
-    const int t = (int)(row - b * T) + p.shift;
-    return (t < 0 || t >= T) ? -1 : b * T + t;
-}
-
-// C[M, N] = beta * C + sum_p A_p[M, K_p] B_p[K_p, N]   (optionally masked: C *= (mask > 0))
-// Staging: thread (row rr = tid / 4, k quarter q = tid % 4) loads 8 consecutive k of one row as two
-// 16-byte loads (operands are 16-byte aligned with row strides a multiple of 4 floats).
-__global__ __launch_bounds__(256) void gemm_rows_kernel(GemmRowsArgs a) {
-    __shared__ float As[GT][GK + 1];
-    __shared__ float Bs[GK][GT + 1];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;            // wave tile 32 x 32 inside the 64 x 64 block
-    const int ntn = a.N / GT;
-    const int64_t row0 = (int64_t)(blockIdx.x / ntn) * GT;
-    const int col0 = (blockIdx.x % ntn) * GT;
-    const int rr = tid >> 2, kq = 8 * (tid & 3);
-    floatx16 acc = {};
-    for (int p = 0; p < a.nparts; ++p) {
-        const APart& ap = a.A[p];
-        const BPart& bp = a.B[p];
-        const int64_t src = part_row(ap, row0 + rr, a.T);
-        const float* arow = src < 0 ? nullptr : ap.ptr + src * ap.ld + kq;
-        for (int k0 = 0; k0 < ap.K; k0 += GK) {
-            float4 v0 = make_float4(0.f, 0.f, 0.f, 0.f), v1 = v0;
-            if (arow) {
-                v0 = *(const float4*)(arow + k0);
-                v1 = *(const float4*)(arow + k0 + 4);
-            }
-            for (int i = tid; i < GK * GT; i += 256) {
-                const int kk = i / GT, nn = i % GT;
-                Bs[kk][nn] = bp.ptr[(int64_t)(k0 + kk) * bp.ld + (int64_t)(col0 + nn) * bp.es];
-            }
-            As[rr][kq + 0] = v0.x; As[rr][kq + 1] = v0.y; As[rr][kq + 2] = v0.z; As[rr][kq + 3] = v0.w;
-            As[rr][kq + 4] = v1.x; As[rr][kq + 5] = v1.y; As[rr][kq + 6] = v1.z; As[rr][kq + 7] = v1.w;
-            __syncthreads();
-#pragma unroll
-            for (int kk = 0; kk < GK; kk += 2) {
-                const float av = As[32 * wr + (lane & 31)][kk + (lane >> 5)];
-                const float bv = Bs[kk + (lane >> 5)][32 * wc + (lane & 31)];
-                acc = MFMA32(av, bv, acc);
-            }
-            __syncthreads();
-        }
-    }
-    const int n = col0 + 32 * wc + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int64_t row = row0 + 32 * wr + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-        const int64_t o = row * a.ldc + n;
-        float v = acc[i];
-        if (a.bias) v += a.bias[n];
-        if (a.beta != 0.f) v += a.beta * a.C[o];
-        if (a.mask) v = (a.mask[row * a.ldm + n] > 0.f) ? v : 0.f;
-        a.C[o] = v;
-    }
-}
-
-// ---- the same row GEMM with bf16 operands (fp32 accumulation), for BF16/FP8 models: B is packed
+// ---- row GEMM: C[M, N] = beta * C + sum_p A_p[M, K_p] B_p[K_p, N] (optionally masked: C *= (mask > 0)), in
+// two forms. With bf16 operands (fp32 accumulation), for BF16/FP8 models: B is packed
 // once per call into bt in MFMA fragment order (parts stacked along k), so a wave's B fragment is one
 // 1 KB load from L2; A rows are read from HBM once per 128 x 128 output tile and rounded to bf16 as
 // they are staged.
@@ -101,6 +31,14 @@ __device__ inline void gate_bwd_one(float pf, float pg, float d, uint16_t& g, ui
     g = __builtin_bit_cast(uint16_t, (__bf16)(th * sg));
     df = __builtin_bit_cast(uint16_t, (__bf16)(d * sg * (1.f - th * th)));
     dgt = __builtin_bit_cast(uint16_t, (__bf16)(d * th * sg * (1.f - sg)));
+}
+
+// The same in fp32.
+__device__ inline void gate_bwd_f32(float pf, float pg, float d, float& g, float& df, float& dgt) {
+    const float th = tanhf(pf), sg = 1.f / (1.f + expf(-pg));
+    g = th * sg;
+    df = d * sg * (1.f - th * th);
+    dgt = d * th * sg * (1.f - sg);
 }
 
 // bt in MFMA fragment order: the 16-byte fragment of lane (h, r) for column tile nt (32 columns) and
@@ -134,6 +72,117 @@ __device__ inline u32x2 bf16_pack4(u32x4 v) {
     return __builtin_bit_cast(u32x2, __builtin_convertvector(__builtin_bit_cast(floatx4, v), bf16x4));
 }
 
+constexpr int EP = BN + 4;     // floats per row of the epilogue's LDS stage
+
+// The row GEMMs' epilogue: the block's 64 RB x 128 tile (wave (wr, wc): rows 32 RB wr .. + 32 RB, columns
+// 64 wc .. + 64) staged through LDS 64 rows at a time; each thread then takes 4 consecutive columns (cq) of 8 rows, all
+// its loads (C for beta, the mask, or the gate's pre-activations) issued before the first store.
+template <int RB>
+__device__ __forceinline__ void rows_epilogue(const GemmRowsArgs& a, const floatx16 (&acc)[RB][2], float* Ep, int64_t row0,
+                                              int col0) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wr = wave & 1, wc = wave >> 1, r = lane & 31, h = lane >> 5;
+    const int cq = 4 * (tid & 31);
+    const int n4 = col0 + cq;
+    for (int pass = 0; pass < RB; ++pass) {
+        __syncthreads();  // the products' (or the previous pass's) LDS reads are done
+        if (RB == 1 || wr == pass) {
+#pragma unroll
+            for (int i = 0; i < RB; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e)
+                        Ep[(32 * (RB == 1 ? wr : i) + 8 * (e >> 2) + 4 * h + (e & 3)) * EP + 64 * wc + 32 * c + r] = acc[i][c][e];
+        }
+        __syncthreads();
+        const int64_t rbase = row0 + 64 * pass + (tid >> 5);   // + 8 it
+        if (a.gpre) {
+            // gate backward (N = 128, one column block): g, dpre from the bf16 pre-activations and dg
+            u32x2 pf[8], pg[8];
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {
+                const int64_t row = rbase + 8 * it;
+                pf[it] = *(const u32x2*)(a.gpre + row * 2 * kC + cq);
+                pg[it] = *(const u32x2*)(a.gpre + row * 2 * kC + kC + cq);
+            }
+#pragma unroll
+            for (int it = 0; it < 8; ++it) {
+                const int64_t row = rbase + 8 * it;
+                const float4 d = *(const float4*)&Ep[(8 * it + (tid >> 5)) * EP + cq];
+                const float fv[4] = {__uint_as_float(pf[it][0] << 16), __uint_as_float(pf[it][0] & 0xffff0000u),
+                                     __uint_as_float(pf[it][1] << 16), __uint_as_float(pf[it][1] & 0xffff0000u)};
+                const float gv[4] = {__uint_as_float(pg[it][0] << 16), __uint_as_float(pg[it][0] & 0xffff0000u),
+                                     __uint_as_float(pg[it][1] << 16), __uint_as_float(pg[it][1] & 0xffff0000u)};
+                const float dv[4] = {d.x, d.y, d.z, d.w};
+                uint16_t go[4], fo[4], so[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) gate_bwd_one(fv[j], gv[j], dv[j], go[j], fo[j], so[j]);
+                *(uint2*)(a.g16 + row * kC + cq) = make_uint2(go[0] | ((uint32_t)go[1] << 16), go[2] | ((uint32_t)go[3] << 16));
+                *(uint2*)(a.dpre16 + row * 2 * kC + cq) =
+                    make_uint2(fo[0] | ((uint32_t)fo[1] << 16), fo[2] | ((uint32_t)fo[3] << 16));
+                *(uint2*)(a.dpre16 + row * 2 * kC + kC + cq) =
+                    make_uint2(so[0] | ((uint32_t)so[1] << 16), so[2] | ((uint32_t)so[3] << 16));
+                if (a.C) *(float4*)(a.C + row * a.ldc + cq) = d;
+            }
+            continue;
+        }
+        if (a.gpre32) {
+            // the same in fp32
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                float4 pf[4], pg[4];
+#pragma unroll
+                for (int it = 0; it < 4; ++it) {
+                    const int64_t row = rbase + 8 * (4 * q + it);
+                    pf[it] = *(const float4*)(a.gpre32 + row * 2 * kC + cq);
+                    pg[it] = *(const float4*)(a.gpre32 + row * 2 * kC + kC + cq);
+                }
+#pragma unroll
+                for (int it = 0; it < 4; ++it) {
+                    const int64_t row = rbase + 8 * (4 * q + it);
+                    const float4 d = *(const float4*)&Ep[(8 * (4 * q + it) + (tid >> 5)) * EP + cq];
+                    const float fv[4] = {pf[it].x, pf[it].y, pf[it].z, pf[it].w}, gv[4] = {pg[it].x, pg[it].y, pg[it].z, pg[it].w};
+                    const float dv[4] = {d.x, d.y, d.z, d.w};
+                    float go[4], fo[4], so[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) gate_bwd_f32(fv[j], gv[j], dv[j], go[j], fo[j], so[j]);
+                    *(float4*)(a.g32 + row * kC + cq) = make_float4(go[0], go[1], go[2], go[3]);
+                    *(float4*)(a.dpre32 + row * 2 * kC + cq) = make_float4(fo[0], fo[1], fo[2], fo[3]);
+                    *(float4*)(a.dpre32 + row * 2 * kC + kC + cq) = make_float4(so[0], so[1], so[2], so[3]);
+                    if (a.C) *(float4*)(a.C + row * a.ldc + cq) = d;
+                }
+            }
+            continue;
+        }
+        float4 cv[8], mv[8];
+        if (a.beta != 0.f) {
+#pragma unroll
+            for (int it = 0; it < 8; ++it) cv[it] = *(const float4*)(a.C + (rbase + 8 * it) * a.ldc + n4);
+        }
+        if (a.mask) {
+#pragma unroll
+            for (int it = 0; it < 8; ++it) mv[it] = *(const float4*)(a.mask + (rbase + 8 * it) * a.ldm + n4);
+        }
+        const float4 bv = a.bias ? *(const float4*)(a.bias + n4) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int it = 0; it < 8; ++it) {
+            const float4 d = *(const float4*)&Ep[(8 * it + (tid >> 5)) * EP + cq];
+            float v[4] = {d.x, d.y, d.z, d.w};
+            const float b4[4] = {bv.x, bv.y, bv.z, bv.w};
+            const float c4[4] = {cv[it].x, cv[it].y, cv[it].z, cv[it].w};
+            const float m4[4] = {mv[it].x, mv[it].y, mv[it].z, mv[it].w};
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if (a.bias) v[j] += b4[j];
+                if (a.beta != 0.f) v[j] += a.beta * c4[j];
+                if (a.mask) v[j] = (m4[j] > 0.f) ? v[j] : 0.f;
+            }
+            *(float4*)(a.C + (rbase + 8 * it) * a.ldc + n4) = make_float4(v[0], v[1], v[2], v[3]);
+        }
+    }
+}
+
 // One block: 128 rows x 128 columns; wave (wr, wc) owns rows 64 wr .. + 64 (two row blocks) and columns
 // 64 wc .. + 64 (two column tiles), so each B fragment feeds two products and each A fragment two.
 // The next chunk's A rows are requested before the current chunk's products, and the chunk's B
@@ -147,7 +196,6 @@ __device__ inline void rows_chunk(const GemmRowsArgs& a, int ci, int& p, int& k0
     k0 = BK * (ci < n0 ? ci : ci - n0);
 }
 
-constexpr int EP = BN + 4;     // floats per row of the epilogue's LDS stage
 constexpr int ROWS_LDS = (64 * EP * 4 > BR2 * AROW * 2) ? 64 * EP * 4 : BR2 * AROW * 2;
 
 __global__ __launch_bounds__(256) void gemm_rows_bf16_kernel(GemmRowsArgs a, int Ktot) {
@@ -241,81 +289,98 @@ __global__ __launch_bounds__(256) void gemm_rows_bf16_kernel(GemmRowsArgs a, int
                     acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bf[s4][c], acc[i][c], 0, 0, 0);
         }
     }
-    // epilogue: the 128 x 128 tile staged through LDS 64 rows at a time; each thread then takes 4
-    // consecutive columns (cq) of 8 rows, all its loads (C for beta, the mask, or the gate's
-    // pre-activations) issued before the first store
-    float* Ep = (float*)smem;
-    const int cq = 4 * (tid & 31);
-    const int n4 = col0 + cq;
-    for (int pass = 0; pass < 2; ++pass) {
-        __syncthreads();  // the products' (or the previous pass's) LDS reads are done
-        if (wr == pass) {
+    rows_epilogue<2>(a, acc, (float*)smem, row0, col0);
+}
+
+// The row GEMM in fp32 (v_mfma_f32_32x32x2f32), for FP32 models and the training forward's head: the same
+// tile, waves and epilogue, chunks of 32 k. B is packed once per call so that a lane's operands of four
+// steps are one 16-byte load; A rows go through LDS at a stride of 33 floats (conflict-free operand reads).
+// Products per output in k order. The matrix cores bound it: 32,768 rows x 512 x 128 take 28 us at 154
+// TFLOP/s and 45 us here; the 63 products of a backward over them 2.4 ms with the gate's backward in the
+// epilogue (64 x 64 tiles, B read from the canonical weights by every block: 3.6 ms and 0.6 ms for the gate).
+// RB = 1, 64 rows per block, while 128 would leave a block or less per CU (32,768 rows: 42 | 39 us on average).
+constexpr int FK = 32, FLD = FK + 1;
+__global__ __launch_bounds__(256) void pack_btf_kernel(GemmRowsArgs a, int Ktot) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;  // i = n Ktot + k
+    if (i >= (int64_t)a.N * Ktot) return;
+    const int n = (int)(i / Ktot);
+    const int kk = (int)(i - (int64_t)n * Ktot);
+    int k = kk, p = 0;
+    while (p + 1 < a.nparts && k >= a.A[p].K) {
+        k -= a.A[p].K;
+        ++p;
+    }
+    const BPart& bp = a.B[p];
+    // column tile, group of 8 k, lane (h = k & 1, column), step of the group
+    const int64_t f = (((int64_t)(n >> 5) * (Ktot >> 3) + (kk >> 3)) * 64 + (kk & 1) * 32 + (n & 31)) * 4 + ((kk & 7) >> 1);
+    a.btf[f] = bp.ptr[(int64_t)k * bp.ld + (int64_t)n * bp.es];
+}
+
+template <int RB>
+__global__ __launch_bounds__(256) void gemm_rows_f32_kernel(GemmRowsArgs a, int Ktot) {
+    __shared__ __attribute__((aligned(16))) float smem[64 * EP];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wr = wave & 1, wc = wave >> 1, r = lane & 31, h = lane >> 5;
+    const int ntn = a.N / BN;
+    const int64_t row0 = (int64_t)(blockIdx.x / ntn) * 64 * RB;
+    const int col0 = (blockIdx.x % ntn) * BN;
+    const int t0 = (int)(row0 % a.T);
+    const int sr = tid >> 3, sc = tid & 7;   // staging: rows sr + 32 i, k 4 sc .. + 4
+    int tw[2 * RB];
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2 * RB; ++i) {
+        int t = t0 + sr + 32 * i;
+        while (t >= a.T) t -= a.T;
+        tw[i] = t;
+    }
+    auto row_ok = [&](int sh, int i) { return (unsigned)(tw[i] + sh) < (unsigned)a.T; };
+    const int nch = Ktot / FK, n0 = a.A[0].K / FK;
+    auto load = [&](int ci, float4 (&raw)[2 * RB]) __attribute__((always_inline)) {
+        const APart& ap = a.A[ci < n0 ? 0 : 1];
+        const int k0 = FK * (ci < n0 ? ci : ci - n0);
 #pragma unroll
-                for (int c = 0; c < 2; ++c)
+        for (int i = 0; i < 2 * RB; ++i)   // (rows whose source leaves the window read the unshifted row and are zeroed below)
+            raw[i] = *(const float4*)(ap.ptr + (row0 + sr + 32 * i + (row_ok(ap.shift, i) ? ap.shift : 0)) * ap.ld + k0 + 4 * sc);
+    };
+    const float* bfr = a.btf + ((int64_t)((col0 + 64 * wc) >> 5) * (Ktot >> 3) * 64 + lane) * 4;
+    const int64_t ctile = (int64_t)(Ktot >> 3) * 64 * 4;
+    floatx16 acc[RB][2] = {};
+    float4 raw[2 * RB];
+    load(0, raw);
+    for (int ci = 0; ci < nch; ++ci) {
+        float4 bf[4][2];
 #pragma unroll
-                    for (int e = 0; e < 16; ++e)
-                        Ep[(32 * i + 8 * (e >> 2) + 4 * h + (e & 3)) * EP + 64 * wc + 32 * c + r] = acc[i][c][e];
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) bf[g][c] = *(const float4*)(bfr + c * ctile + (int64_t)(4 * ci + g) * 64 * 4);
+        __syncthreads();  // the previous chunk's operands are read
+        const int sh = a.A[ci < n0 ? 0 : 1].shift;
+#pragma unroll
+        for (int i = 0; i < 2 * RB; ++i) {
+            const bool ok = row_ok(sh, i);
+            float* dst = &smem[(sr + 32 * i) * FLD + 4 * sc];
+            dst[0] = ok ? raw[i].x : 0.f;
+            dst[1] = ok ? raw[i].y : 0.f;
+            dst[2] = ok ? raw[i].z : 0.f;
+            dst[3] = ok ? raw[i].w : 0.f;
         }
         __syncthreads();
-        const int64_t rbase = row0 + 64 * pass + (tid >> 5);   // + 8 it
-        if (a.gpre) {
-            // gate backward (N = 128, one column block): g, dpre from the bf16 pre-activations and dg
-            u32x2 pf[8], pg[8];
+        if (ci + 1 < nch) load(ci + 1, raw);   // in flight during this chunk's products
 #pragma unroll
-            for (int it = 0; it < 8; ++it) {
-                const int64_t row = rbase + 8 * it;
-                pf[it] = *(const u32x2*)(a.gpre + row * 2 * kC + cq);
-                pg[it] = *(const u32x2*)(a.gpre + row * 2 * kC + kC + cq);
+        for (int s = 0; s < FK / 2; ++s) {
+            float av[RB];
+#pragma unroll
+            for (int i = 0; i < RB; ++i) av[i] = smem[(32 * RB * wr + 32 * i + r) * FLD + 2 * s + h];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const float4& b4 = bf[s >> 2][c];
+                const float bv = (s & 3) == 0 ? b4.x : (s & 3) == 1 ? b4.y : (s & 3) == 2 ? b4.z : b4.w;
+#pragma unroll
+                for (int i = 0; i < RB; ++i) acc[i][c] = MFMA32(av[i], bv, acc[i][c]);
             }
-#pragma unroll
-            for (int it = 0; it < 8; ++it) {
-                const int64_t row = rbase + 8 * it;
-                const float4 d = *(const float4*)&Ep[(8 * it + (tid >> 5)) * EP + cq];
-                const float fv[4] = {__uint_as_float(pf[it][0] << 16), __uint_as_float(pf[it][0] & 0xffff0000u),
-                                     __uint_as_float(pf[it][1] << 16), __uint_as_float(pf[it][1] & 0xffff0000u)};
-                const float gv[4] = {__uint_as_float(pg[it][0] << 16), __uint_as_float(pg[it][0] & 0xffff0000u),
-                                     __uint_as_float(pg[it][1] << 16), __uint_as_float(pg[it][1] & 0xffff0000u)};
-                const float dv[4] = {d.x, d.y, d.z, d.w};
-                uint16_t go[4], fo[4], so[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) gate_bwd_one(fv[j], gv[j], dv[j], go[j], fo[j], so[j]);
-                *(uint2*)(a.g16 + row * kC + cq) = make_uint2(go[0] | ((uint32_t)go[1] << 16), go[2] | ((uint32_t)go[3] << 16));
-                *(uint2*)(a.dpre16 + row * 2 * kC + cq) =
-                    make_uint2(fo[0] | ((uint32_t)fo[1] << 16), fo[2] | ((uint32_t)fo[3] << 16));
-                *(uint2*)(a.dpre16 + row * 2 * kC + kC + cq) =
-                    make_uint2(so[0] | ((uint32_t)so[1] << 16), so[2] | ((uint32_t)so[3] << 16));
-                if (a.C) *(float4*)(a.C + row * a.ldc + cq) = d;
-            }
-            continue;
-        }
-        float4 cv[8], mv[8];
-        if (a.beta != 0.f) {
-#pragma unroll
-            for (int it = 0; it < 8; ++it) cv[it] = *(const float4*)(a.C + (rbase + 8 * it) * a.ldc + n4);
-        }
-        if (a.mask) {
-#pragma unroll
-            for (int it = 0; it < 8; ++it) mv[it] = *(const float4*)(a.mask + (rbase + 8 * it) * a.ldm + n4);
-        }
-        const float4 bv = a.bias ? *(const float4*)(a.bias + n4) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int it = 0; it < 8; ++it) {
-            const float4 d = *(const float4*)&Ep[(8 * it + (tid >> 5)) * EP + cq];
-            float v[4] = {d.x, d.y, d.z, d.w};
-            const float b4[4] = {bv.x, bv.y, bv.z, bv.w};
-            const float c4[4] = {cv[it].x, cv[it].y, cv[it].z, cv[it].w};
-            const float m4[4] = {mv[it].x, mv[it].y, mv[it].z, mv[it].w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (a.bias) v[j] += b4[j];
-                if (a.beta != 0.f) v[j] += a.beta * c4[j];
-                if (a.mask) v[j] = (m4[j] > 0.f) ? v[j] : 0.f;
-            }
-            *(float4*)(a.C + (rbase + 8 * it) * a.ldc + n4) = make_float4(v[0], v[1], v[2], v[3]);
         }
     }
+    rows_epilogue<RB>(a, acc, smem, row0, col0);
 }
 
 // Block -> (output tile, row chunk) of the weight-gradient GEMMs. Blocks are dispatched round-robin
@@ -328,182 +393,12 @@ __device__ inline void wgrad_block(int ntiles, int& tile, int& chunk) {
     chunk = (idx / ntiles) * 8 + xcd;
 }
 
-// part[chunk][K][N] = sum over the chunk's rows of A(row, k) B(row, n); A from row-shifted parts
-// stacked along k, B plain. One block: one 64 x 64 output tile of one row chunk.
-__global__ __launch_bounds__(256) void gemm_wgrad_kernel(WgradArgs a) {
-    __shared__ float As[GK][GT + 1];   // [row][k]
-    __shared__ float Bs[GK][GT + 1];   // [row][n]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1;
-    const int ntn = a.N / GT, ntk = a.Ktot / GT;
-    int tile, chunk;
-    wgrad_block(ntn * ntk, tile, chunk);
-    if ((int64_t)chunk * a.rows_per_chunk >= a.M) return;  // padding of the grid (uniform per block)
-    const int k0 = (tile / ntn) * GT, n0 = (tile % ntn) * GT;
-    // which A part holds columns [k0, k0 + 64)
-    int p = 0, kb = 0;
-    while (kb + a.A[p].K <= k0) {
-        kb += a.A[p].K;
-        ++p;
-    }
-    const APart ap = a.A[p];
-    const int64_t r0 = (int64_t)chunk * a.rows_per_chunk;
-    const int64_t r1 = min(r0 + a.rows_per_chunk, a.M);
-    // staging: thread (row rr = tid / 8, column group c8 = 8 (tid % 8)) loads 8 consecutive columns
-    // of A (columns k0 - kb + c8 ..) and of B (n0 + c8 ..) of one row, two 16-byte loads each
-    const int rr = tid >> 3, c8 = 8 * (tid & 7);
-    const APart bpart{a.B, a.ldb, a.bshift, a.N};
-    floatx16 acc = {};
-    for (int64_t rb = r0; rb < r1; rb += GK) {
-        const int64_t row = rb + rr;
-        float4 x0 = make_float4(0.f, 0.f, 0.f, 0.f), x1 = x0, y0 = x0, y1 = x0;
-        if (row < r1) {
-            const int64_t sa = part_row(ap, row, a.T), sb = part_row(bpart, row, a.T);
-            if (sa >= 0) {
-                const float* pa = ap.ptr + sa * ap.ld + (k0 - kb) + c8;
-                x0 = *(const float4*)pa;
-                x1 = *(const float4*)(pa + 4);
-            }
-            if (sb >= 0) {
-                const float* pb = a.B + sb * a.ldb + n0 + c8;
-                y0 = *(const float4*)pb;
-                y1 = *(const float4*)(pb + 4);
-            }
-        }
-        As[rr][c8 + 0] = x0.x; As[rr][c8 + 1] = x0.y; As[rr][c8 + 2] = x0.z; As[rr][c8 + 3] = x0.w;
-        As[rr][c8 + 4] = x1.x; As[rr][c8 + 5] = x1.y; As[rr][c8 + 6] = x1.z; As[rr][c8 + 7] = x1.w;
-        Bs[rr][c8 + 0] = y0.x; Bs[rr][c8 + 1] = y0.y; Bs[rr][c8 + 2] = y0.z; Bs[rr][c8 + 3] = y0.w;
-        Bs[rr][c8 + 4] = y1.x; Bs[rr][c8 + 5] = y1.y; Bs[rr][c8 + 6] = y1.z; Bs[rr][c8 + 7] = y1.w;
-        __syncthreads();
-#pragma unroll
-        for (int r2 = 0; r2 < GK; r2 += 2) {
-            const float av = As[r2 + (lane >> 5)][32 * wr + (lane & 31)];   // A^T: (k, row)
-            const float bv = Bs[r2 + (lane >> 5)][32 * wc + (lane & 31)];
-            acc = MFMA32(av, bv, acc);
-        }
-        __syncthreads();
-    }
-    float* out = a.part + (int64_t)chunk * a.Ktot * a.N;
-    const int n = n0 + 32 * wc + (lane & 31);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int k = k0 + 32 * wr + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
-        out[(int64_t)k * a.N + n] = acc[i];
-    }
-}
-
-// The same partial sums with bf16 operands (rounded to nearest even) and fp32 accumulation, for
-// BF16/FP8 members: v_mfma_f32_32x32x16_bf16 with the data rows as the contraction. Each step
-// stages 64 rows of A and B, converts them to bf16 and stores them transposed in LDS ([column][row],
-// 144-byte rows), so that a lane reads the 8 consecutive rows of its fragment as one 16-byte word;
-// the next step's rows are loaded during this step's products. Same tiles, chunks and partials as
-// gemm_wgrad_kernel.
-constexpr int WB_ROWS = 64;                // rows per step
-constexpr int WB_LD = WB_ROWS * 2 + 16;    // bytes per transposed LDS row
-__global__ __launch_bounds__(256) void gemm_wgrad_bf16_kernel(WgradArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t At[GT * WB_LD];   // [k][row] bf16
-    __shared__ __attribute__((aligned(16))) uint8_t Bt[GT * WB_LD];   // [n][row] bf16
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wr = wave >> 1, wc = wave & 1, h = lane >> 5, r = lane & 31;
-    const int ntn = a.N / GT, ntk = a.Ktot / GT;
-    int tile, chunk;
-    wgrad_block(ntn * ntk, tile, chunk);
-    if ((int64_t)chunk * a.rows_per_chunk >= a.M) return;  // padding of the grid (uniform per block)
-    const int k0 = (tile / ntn) * GT, n0 = (tile % ntn) * GT;
-    int p = 0, kb = 0;
-    while (kb + a.A[p].K <= k0) {
-        kb += a.A[p].K;
-        ++p;
-    }
-    const APart ap = a.A[p];
-    const APart bpart{a.B, a.ldb, a.bshift, a.N};
-    const int64_t r0 = (int64_t)chunk * a.rows_per_chunk;
-    const int64_t r1 = min(r0 + a.rows_per_chunk, a.M);
-    // staging: thread (row pair rp = tid / 8, column group c8 = 8 (tid % 8)) loads 8 consecutive
-    // columns of rows 2 rp and 2 rp + 1, of A and of B
-    const int rp = tid >> 3, c8 = 8 * (tid & 7);
-    float4 ra[2][2], rbv[2][2];
-    uint4 ra16[2], rb16[2];  // A / B rows already in bf16
-    auto load = [&](int64_t rb) {
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const int64_t row = rb + 2 * rp + e;
-            ra[e][0] = ra[e][1] = rbv[e][0] = rbv[e][1] = make_float4(0.f, 0.f, 0.f, 0.f);
-            ra16[e] = rb16[e] = make_uint4(0, 0, 0, 0);
-            if (row < r1) {
-                const int64_t sa = part_row(ap, row, a.T), sb = part_row(bpart, row, a.T);
-                if (sa >= 0) {
-                    if (ap.p16) {
-                        ra16[e] = *(const uint4*)(ap.p16 + sa * ap.ld + (k0 - kb) + c8);
-                    } else {
-                        const float* pa = ap.ptr + sa * ap.ld + (k0 - kb) + c8;
-                        ra[e][0] = *(const float4*)pa;
-                        ra[e][1] = *(const float4*)(pa + 4);
-                    }
-                }
-                if (sb >= 0) {
-                    if (a.B16) {
-                        rb16[e] = *(const uint4*)(a.B16 + sb * a.ldb + n0 + c8);
-                    } else {
-                        const float* pb = a.B + sb * a.ldb + n0 + c8;
-                        rbv[e][0] = *(const float4*)pb;
-                        rbv[e][1] = *(const float4*)(pb + 4);
-                    }
-                }
-            }
-        }
-    };
-    // the same for rows given in bf16: column c of the two rows as one pair
-    auto put16 = [&](uint8_t* dst, const uint4 (&v)[2]) {
-        const uint32_t w0[4] = {v[0].x, v[0].y, v[0].z, v[0].w};
-        const uint32_t w1[4] = {v[1].x, v[1].y, v[1].z, v[1].w};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            *(uint32_t*)(dst + (c8 + 2 * j) * WB_LD + 4 * rp) = (w0[j] & 0xffffu) | (w1[j] << 16);
-            *(uint32_t*)(dst + (c8 + 2 * j + 1) * WB_LD + 4 * rp) = (w0[j] >> 16) | (w1[j] & 0xffff0000u);
-        }
-    };
-    // column c of rows (2 rp, 2 rp + 1) as one bf16 pair at [c][2 rp]
-    auto put = [&](uint8_t* dst, const float4 (&v)[2][2]) {
-        const float c0[8] = {v[0][0].x, v[0][0].y, v[0][0].z, v[0][0].w, v[0][1].x, v[0][1].y, v[0][1].z, v[0][1].w};
-        const float c1[8] = {v[1][0].x, v[1][0].y, v[1][0].z, v[1][0].w, v[1][1].x, v[1][1].y, v[1][1].z, v[1][1].w};
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t w = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)c0[j]) |
-                               ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)c1[j]) << 16);
-            *(uint32_t*)(dst + (c8 + j) * WB_LD + 4 * rp) = w;
-        }
-    };
-    floatx16 acc = {};
-    load(r0);
-    for (int64_t rb = r0; rb < r1; rb += WB_ROWS) {
-        if (ap.p16) put16(At, ra16);
-        else put(At, ra);
-        if (a.B16) put16(Bt, rb16);
-        else put(Bt, rbv);
-        __syncthreads();
-        if (rb + WB_ROWS < r1) load(rb + WB_ROWS);  // in flight during the products
-#pragma unroll
-        for (int s16 = 0; s16 < WB_ROWS / 16; ++s16) {
-            const bf16x8 av = *(const bf16x8*)(At + (32 * wr + r) * WB_LD + 2 * (16 * s16 + 8 * h));
-            const bf16x8 bv = *(const bf16x8*)(Bt + (32 * wc + r) * WB_LD + 2 * (16 * s16 + 8 * h));
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
-        }
-        __syncthreads();
-    }
-    float* out = a.part + (int64_t)chunk * a.Ktot * a.N;
-    const int n = n0 + 32 * wc + r;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-        const int k = k0 + 32 * wr + 8 * (i >> 2) + 4 * h + (i & 3);
-        out[(int64_t)k * a.N + n] = acc[i];
-    }
-}
-
-// The weight-gradient GEMM with bf16 operands on 128 x 128 output tiles, for chunks of one window
-// (T % 64 == 0): partials identical to gemm_wgrad_bf16_kernel's (every output takes the same MFMAs in
-// the same order: 64-row steps, then 16-row groups, ascending), with four times the products per
-// staged byte. Waves 0-1 stage the A tile, waves 2-3 the B tile: a thread loads 8 rows x 8 columns
+// Weight-gradient GEMMs: part[chunk][K][N] = sum over the chunk's rows of A(row, k) B(row, n), A from parts
+// stacked along k, B from one or two row-shifted parts stacked along n, on 128 x 128 output tiles. A chunk
+// is a run of rows_per_chunk rows of one window.
+//
+// With bf16 operands (rounded to nearest even, fp32 accumulation; 64-row steps, then 16-row groups,
+// ascending): waves 0-1 stage the A tile, waves 2-3 the B tile: a thread loads 8 rows x 8 columns
 // (one 16-byte load per row for bf16, two for fp32), transposes them in registers and writes 8
 // columns of 8 rows as 16-byte words into LDS ([column][row], 144-byte columns: conflict-free
 // writes and fragment reads). Two LDS buffers, one barrier per step; the next step's rows are
@@ -533,7 +428,8 @@ __global__ __launch_bounds__(256) void gemm_wgrad_t128_kernel(WgradArgs a) {
     const int ntn = a.N / W2T, ntk = a.Ktot / W2T;
     int tile, chunk;
     wgrad_block(ntn * ntk, tile, chunk);
-    if ((int64_t)chunk * a.T >= a.M) return;  // padding of the grid (uniform per block)
+    const int64_t r0 = (int64_t)chunk * a.rows_per_chunk;
+    if (r0 >= a.M) return;  // padding of the grid (uniform per block)
     const int k0 = (tile / ntn) * W2T, n0 = (tile % ntn) * W2T;
     // this thread's operand: waves 0-1 the A tile (columns k0 ..), waves 2-3 the B tile (n0 ..)
     W2Operand op;
@@ -556,13 +452,14 @@ __global__ __launch_bounds__(256) void gemm_wgrad_t128_kernel(WgradArgs a) {
     col += 8 * cm;
     const bool csum = a.cpart != nullptr && isA && tile % ntn == 0;   // uniform per wave
     float cs[8] = {};
-    const int64_t wrow0 = (int64_t)chunk * a.T;           // the chunk's window
+    const int tb = (int)(r0 % a.T);                        // the chunk's first time step and window
+    const int64_t wrow0 = r0 - tb;
     const bool is16 = op.p16 != nullptr;
     // rows whose shifted source leaves the window read the unshifted row and are zeroed when staged
     auto load = [&](int step, u32x4 (&raw)[16]) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int t = step * W2R + 8 * rg + j;
+            const int t = tb + step * W2R + 8 * rg + j;
             const bool ok = (unsigned)(t + op.shift) < (unsigned)a.T;
             const int64_t row = wrow0 + t + (ok ? op.shift : 0);
             if (is16) {
@@ -578,7 +475,7 @@ __global__ __launch_bounds__(256) void gemm_wgrad_t128_kernel(WgradArgs a) {
         u32x4 w[8];  // row j: columns 8 cm .. + 8 in bf16
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const int t = step * W2R + 8 * rg + j;
+            const int t = tb + step * W2R + 8 * rg + j;
             const bool ok = (unsigned)(t + op.shift) < (unsigned)a.T;
             const u32x4 v = is16 ? raw[2 * j] : w2_bf16x8(raw[2 * j], raw[2 * j + 1]);
             w[j] = ok ? v : u32x4{0, 0, 0, 0};
@@ -603,7 +500,7 @@ __global__ __launch_bounds__(256) void gemm_wgrad_t128_kernel(WgradArgs a) {
     };
     floatx16 acc[2][2] = {};
     u32x4 raw[16];
-    const int nsteps = a.T / W2R;
+    const int nsteps = (int)(a.rows_per_chunk / W2R);
     load(0, raw);
     for (int s = 0; s < nsteps; ++s) {
         uint8_t* buf = lds + (s & 1) * 2 * W2OP;
@@ -650,6 +547,100 @@ __global__ __launch_bounds__(256) void gemm_wgrad_t128_kernel(WgradArgs a) {
             float* o = a.cpart + (int64_t)chunk * a.Ktot + k0 + 8 * cm;
             *(float4*)o = make_float4(cs[0], cs[1], cs[2], cs[3]);
             *(float4*)(o + 4) = make_float4(cs[4], cs[5], cs[6], cs[7]);
+        }
+    }
+}
+
+// The same in fp32 (v_mfma_f32_32x32x2f32; rows ascending, two per step), for FP32 models: 32-row steps staged
+// as they are ([row][column], a stride of 160 floats puts the two rows of a step in different banks), two
+// LDS buffers, one barrier per step. The matrix cores bound it: 32,768 rows x 256 x 256 take 28 us at 154
+// TFLOP/s and 46 us here. In 64 x 64 tiles with one chunk per window the 91 products of a backward over
+// 8 windows of 4,096 took 14.5 ms (160 us each), the 61 of these tiles 2.2 ms.
+constexpr int WFR = 32, WFLD = 160;
+__global__ __launch_bounds__(256) void gemm_wgrad_f32_kernel(WgradArgs a) {
+    __shared__ __attribute__((aligned(16))) float lds[2][2][WFR * WFLD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wk = wave & 1, wn = wave >> 1, h = lane >> 5, r = lane & 31;
+    const int ntn = a.N / W2T, ntk = a.Ktot / W2T;
+    int tile, chunk;
+    wgrad_block(ntn * ntk, tile, chunk);
+    const int64_t r0 = (int64_t)chunk * a.rows_per_chunk;
+    if (r0 >= a.M) return;  // padding of the grid (uniform per block)
+    const int k0 = (tile / ntn) * W2T, n0 = (tile % ntn) * W2T;
+    int p = 0, kb = 0;
+    while (kb + a.A[p].K <= k0) {
+        kb += a.A[p].K;
+        ++p;
+    }
+    const int nb = a.N / a.nbparts, q = n0 / nb;
+    const int rr = tid >> 5, c4 = 4 * (tid & 31);   // staging: rows rr + 8 i, four columns of each operand
+    const float* pa = a.A[p].ptr + k0 - kb + c4;
+    const float* pb = a.B + n0 - q * nb + c4;
+    const int64_t lda = a.A[p].ld, ldb = a.ldb;
+    const int sa = a.A[p].shift, sb = q ? a.bshift1 : a.bshift;
+    const bool csum = a.cpart != nullptr && tile % ntn == 0;   // uniform over the block
+    floatx4 cs = {};
+    const int tb = (int)(r0 % a.T);
+    const int64_t wrow0 = r0 - tb;
+    floatx4 ra[4], rb[4];
+    auto load = [&](int step) __attribute__((always_inline)) {   // (rows outside the window read the unshifted row)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = tb + step * WFR + rr + 8 * i;
+            ra[i] = *(const floatx4*)(pa + (wrow0 + t + ((unsigned)(t + sa) < (unsigned)a.T ? sa : 0)) * lda);
+            rb[i] = *(const floatx4*)(pb + (wrow0 + t + ((unsigned)(t + sb) < (unsigned)a.T ? sb : 0)) * ldb);
+        }
+    };
+    floatx16 acc[2][2] = {};
+    const int nsteps = (int)(a.rows_per_chunk / WFR);
+    const floatx4 zero = {};
+    load(0);
+    for (int s = 0; s < nsteps; ++s) {
+        float* At = lds[s & 1][0];
+        float* Bt = lds[s & 1][1];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int t = tb + s * WFR + rr + 8 * i;
+            const floatx4 va = (unsigned)(t + sa) < (unsigned)a.T ? ra[i] : zero;
+            *(floatx4*)&At[(rr + 8 * i) * WFLD + c4] = va;
+            *(floatx4*)&Bt[(rr + 8 * i) * WFLD + c4] = (unsigned)(t + sb) < (unsigned)a.T ? rb[i] : zero;
+            if (csum) cs += va;
+        }
+        __syncthreads();
+        if (s + 1 < nsteps) load(s + 1);   // in flight during the products
+#pragma unroll
+        for (int r2 = 0; r2 < WFR; r2 += 2) {
+            float av[2], bv[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                av[i] = At[(r2 + h) * WFLD + 64 * wk + 32 * i + r];
+                bv[i] = Bt[(r2 + h) * WFLD + 64 * wn + 32 * i + r];
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c) acc[i][c] = MFMA32(av[i], bv[c], acc[i][c]);
+        }
+    }
+    float* out = a.part + (int64_t)chunk * a.Ktot * a.N;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const int n = n0 + 64 * wn + 32 * c + r;
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                out[(int64_t)(k0 + 64 * wk + 32 * i + 8 * (e >> 2) + 4 * h + (e & 3)) * a.N + n] = acc[i][c][e];
+        }
+    if (csum) {   // the eight row groups' sums, in order
+        __syncthreads();
+        floatx4* red = (floatx4*)lds;
+        red[tid] = cs;
+        __syncthreads();
+        if (tid < 32) {
+            floatx4 t = red[tid];
+            for (int k = 1; k < 8; ++k) t += red[32 * k + tid];
+            *(floatx4*)(a.cpart + (int64_t)chunk * a.Ktot + k0 + c4) = t;
         }
     }
 }
@@ -713,28 +704,28 @@ static hipError_t reduce_parts(float* part, int64_t part_capacity, int nchunks, 
     return reduce_parts(part, part_capacity, nchunks, KN, (int)KN, WgradDst{dst, nullptr, KN, stride, false}, st);
 }
 
-// part[chunk][n] = sum over the chunk's rows of f(X[row][n]) * w(row); f = identity or ReLU
-__global__ __launch_bounds__(256) void colsum_kernel(const float* X, int64_t ldx, int64_t M, int N,
-                                                     const float* w, int64_t wstride, int relu,
-                                                     int64_t rows_per_chunk, float* part) {
-    const int chunk = blockIdx.y;
-    const int n = blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    const int64_t r0 = (int64_t)chunk * rows_per_chunk;
-    const int64_t r1 = min(r0 + rows_per_chunk, M);
+// part[chunk] = sum over the chunk's rows of X[row ldx]: one column, one block per chunk, each thread its
+// rows in order, then the threads pairwise (the bias of the logit: 524,288 rows in 4.5 us; 0.38 ms with one
+// thread per chunk).
+__global__ __launch_bounds__(256) void colsum1_kernel(const float* X, int64_t ldx, int64_t M, int64_t rows_per_chunk,
+                                                      float* part) {
+    __shared__ float red[256];
+    const int64_t r0 = (int64_t)blockIdx.x * rows_per_chunk, r1 = min(r0 + rows_per_chunk, M);
     float s = 0.f;
-    for (int64_t r = r0; r < r1; ++r) {
-        float v = X[r * ldx + n];
-        if (relu) v = fmaxf(v, 0.f);
-        if (w) v *= w[r * wstride];
-        s += v;
+#pragma unroll 8
+    for (int64_t r = r0 + threadIdx.x; r < r1; r += 256) s += X[r * ldx];
+    red[threadIdx.x] = s;
+    for (int w = 128; w > 0; w >>= 1) {
+        __syncthreads();
+        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     }
-    part[(int64_t)chunk * N + n] = s;
+    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-// The same column sums for 16-byte aligned rows of N = 4 c columns (N <= 1024): one block per chunk,
-// each thread a float4 of columns for every (256 / (N/4))-th row of the chunk, then the row groups
-// added in LDS in a fixed order (the result does not depend on scheduling).
+// part[chunk][n] = sum over the chunk's rows of f(X[row][n]) * w(row), f = identity or ReLU, for 16-byte
+// aligned rows of N = 4 c columns (N <= 1024): one block per chunk, each thread a float4 of columns for every
+// (256 / (N/4))-th row of the chunk, then the row groups added in LDS in a fixed order (the result does
+// not depend on scheduling).
 __global__ __launch_bounds__(256) void colsum4_kernel(const float* X, int64_t ldx, int64_t M, int N,
                                                       const float* w, int64_t wstride, int relu,
                                                       int64_t rows_per_chunk, float* part) {
@@ -766,38 +757,6 @@ __global__ __launch_bounds__(256) void colsum4_kernel(const float* X, int64_t ld
     }
 }
 
-// colsum4_kernel for bf16 X (four columns as one 8-byte load)
-__global__ __launch_bounds__(256) void colsum16_kernel(const uint16_t* X, int64_t ldx, int64_t M, int N,
-                                                       int64_t rows_per_chunk, float* part) {
-    __shared__ float4 red[256];
-    const int cpr = N >> 2;
-    const int groups = 256 / cpr;
-    const int tid = threadIdx.x, c4 = tid % cpr, g = tid / cpr;
-    const int64_t r0 = (int64_t)blockIdx.x * rows_per_chunk;
-    const int64_t r1 = min(r0 + rows_per_chunk, M);
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (g < groups) {
-#pragma unroll 4
-        for (int64_t r = r0 + g; r < r1; r += groups) {
-            const uint2 w = *(const uint2*)(X + r * ldx + 4 * c4);
-            s.x += __uint_as_float(w.x << 16);
-            s.y += __uint_as_float(w.x & 0xffff0000u);
-            s.z += __uint_as_float(w.y << 16);
-            s.w += __uint_as_float(w.y & 0xffff0000u);
-        }
-    }
-    red[tid] = s;
-    __syncthreads();
-    if (tid < cpr) {
-        float4 t = red[tid];
-        for (int k = 1; k < groups; ++k) {
-            const float4 u = red[k * cpr + tid];
-            t.x += u.x; t.y += u.y; t.z += u.z; t.w += u.w;
-        }
-        *(float4*)(part + (int64_t)blockIdx.x * N + 4 * tid) = t;
-    }
-}
-
 // x0[row][c] = W_in[c] . u[row] + b_in[c]   (windows [B][T][2] interleaved)
 __global__ __launch_bounds__(256) void input_proj_kernel(const float* u, int64_t M, const float* w_in,
                                                          const float* b_in, float* x0) {
@@ -806,22 +765,6 @@ __global__ __launch_bounds__(256) void input_proj_kernel(const float* u, int64_t
     const int64_t row = i / kC;
     const int c = (int)(i % kC);
     x0[i] = b_in[c] + w_in[2 * c] * u[2 * row] + w_in[2 * c + 1] * u[2 * row + 1];
-}
-
-// Gate backward: from pre [M][256] and dg [M][128]: g = tanh(pf) sigmoid(pg) [M][128] and
-// dpre = [dg sigmoid(pg) (1 - tanh^2(pf)) | dg tanh(pf) sigmoid(pg) (1 - sigmoid(pg))] [M][256].
-__global__ __launch_bounds__(256) void gate_bwd_kernel(const float* pre, const float* dg, int64_t M, float* g,
-                                                       float* dpre) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= M * kC) return;
-    const int64_t row = i / kC;
-    const int c = (int)(i % kC);
-    const float pf = pre[row * 2 * kC + c], pg = pre[row * 2 * kC + kC + c];
-    const float th = tanhf(pf), sg = 1.f / (1.f + expf(-pg));
-    const float d = dg[i];
-    g[i] = th * sg;
-    dpre[row * 2 * kC + c] = d * sg * (1.f - th * th);
-    dpre[row * 2 * kC + kC + c] = d * th * sg * (1.f - sg);
 }
 
 // Head backward, elementwise part: dh[row][j] = dz[row] * w2[j] * act'(h[row][j]);
@@ -947,90 +890,75 @@ __global__ __launch_bounds__(256) void mean_final_kernel(const double* part, int
 static inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 hipError_t gemm_rows(const GemmRowsArgs& a, hipStream_t st) {
-    bool bf16 = a.bt != nullptr && a.N % BN == 0 && a.M % BR2 == 0 && a.nparts <= 2;
-    bool any16 = false;
+    bool bf16 = a.bt != nullptr && (!a.mask || ((uintptr_t)a.mask & 15) == 0), any16 = false;
     int Ktot = 0;
+    bool ok = a.N % BN == 0 && a.M % BR2 == 0 && a.nparts >= 1 && a.nparts <= 2;
     for (int p = 0; p < a.nparts; ++p) {
         Ktot += a.A[p].K;
         const APart& q = a.A[p];
         any16 = any16 || q.p16;
-        bf16 = bf16 && q.K % BK == 0 &&
-               (q.p16 ? q.ld % 8 == 0 && ((uintptr_t)q.p16 & 15) == 0 : q.ld % 4 == 0 && ((uintptr_t)q.ptr & 15) == 0);
+        bf16 = bf16 && q.K % BK == 0 && (!q.p16 || (q.ld % 8 == 0 && ((uintptr_t)q.p16 & 15) == 0));
+        ok = ok && q.K % FK == 0 && (q.p16 || (q.ld % 4 == 0 && ((uintptr_t)q.ptr & 15) == 0));
     }
-    // the bf16 kernel's epilogue moves 4 columns at a time
-    bf16 = bf16 && (!a.C || (a.ldc % 4 == 0 && ((uintptr_t)a.C & 15) == 0)) &&
-           (!a.mask || (a.ldm % 4 == 0 && ((uintptr_t)a.mask & 15) == 0)) && (!a.bias || ((uintptr_t)a.bias & 15) == 0);
-    if (any16 && !bf16) return hipErrorInvalidValue;  // bf16 parts need the bf16-operand kernel
-    if (a.gpre && (!bf16 || a.N != kC || !a.g16 || !a.dpre16 || a.bias || a.beta != 0.f || a.mask ||
-                   (a.C && a.ldc % 4) || ((uintptr_t)a.gpre & 7)))
+    // the epilogue moves 4 columns at a time
+    ok = ok && (!a.C || (a.ldc % 4 == 0 && ((uintptr_t)a.C & 15) == 0)) && (!a.mask || a.ldm % 4 == 0) &&
+         (!a.bias || ((uintptr_t)a.bias & 15) == 0);
+    if (!ok || (!bf16 && (any16 || !a.btf))) return hipErrorInvalidValue;
+    if (!a.C && !a.gpre && !a.gpre32) return hipErrorInvalidValue;
+    if ((a.gpre || a.gpre32) && (a.N != kC || a.bias || a.beta != 0.f || a.mask)) return hipErrorInvalidValue;
+    if (a.gpre && (!bf16 || !a.g16 || !a.dpre16 || ((uintptr_t)a.gpre & 7))) return hipErrorInvalidValue;
+    if (a.gpre32 && (!a.g32 || !a.dpre32 || (((uintptr_t)a.gpre32 | (uintptr_t)a.g32 | (uintptr_t)a.dpre32) & 15)))
         return hipErrorInvalidValue;
-    if (!a.C && !a.gpre) return hipErrorInvalidValue;
-    if (bf16) {
-        hipLaunchKernelGGL(pack_bt_kernel, dim3((unsigned)(((int64_t)a.N * Ktot + 255) / 256)), dim3(256), 0, st, a,
-                           Ktot);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(gemm_rows_bf16_kernel, dim3((unsigned)((a.M / BR2) * (a.N / BN))), dim3(256), 0, st, a,
-                           Ktot);
-        return hipGetLastError();
-    }
-    const int64_t blocks = (a.M / GT) * (a.N / GT);
-    hipLaunchKernelGGL(gemm_rows_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
+    const dim3 pgrid((unsigned)(((int64_t)a.N * Ktot + 255) / 256)), grid((unsigned)((a.M / BR2) * (a.N / BN)));
+    if (bf16) hipLaunchKernelGGL(pack_bt_kernel, pgrid, dim3(256), 0, st, a, Ktot);
+    else hipLaunchKernelGGL(pack_btf_kernel, pgrid, dim3(256), 0, st, a, Ktot);
+    if (bf16) hipLaunchKernelGGL(gemm_rows_bf16_kernel, grid, dim3(256), 0, st, a, Ktot);
+    else if (grid.x >= 512) hipLaunchKernelGGL(gemm_rows_f32_kernel<2>, grid, dim3(256), 0, st, a, Ktot);
+    else hipLaunchKernelGGL(gemm_rows_f32_kernel<1>, dim3(2 * grid.x), dim3(256), 0, st, a, Ktot);
     return hipGetLastError();
+}
+
+// Rows per chunk: whole windows when they give a block for each of the chip's 512 slots (two per CU), else
+// windows halved, down to 128 rows (two steps of the bf16 kernel). 8 windows of 4,096 rows have 8 chunks
+// otherwise, 32 blocks or fewer; 128 windows the same 512 blocks for the conv taps, but 256 for skip and residual.
+static int64_t wgrad_rows(const WgradArgs& a) {
+    const int64_t tiles = (int64_t)(a.Ktot / W2T) * (a.N / W2T);
+    int64_t rpc = a.T;
+    while ((a.M / rpc) * tiles < 512 && rpc % 256 == 0) rpc /= 2;
+    return rpc;
 }
 
 hipError_t gemm_wgrad(const WgradArgs& a0, const WgradDst& d, hipStream_t st, const WgradDst* cdst) {
     WgradArgs a = a0;
     if ((a.B16 || a.A[0].p16 || (a.nparts > 1 && a.A[1].p16)) && !a.bf16) return hipErrorInvalidValue;
     if (a.nbparts < 1 || a.nbparts > 2 || a.N % a.nbparts) return hipErrorInvalidValue;
-    // the 128 x 128 tile kernel: bf16 operands, chunks of one window, parts in whole tiles, 16-byte rows
-    bool t128 = a.bf16 && a.rows_per_chunk == a.T && a.T % W2R == 0 && a.M % a.T == 0 && a.Ktot % W2T == 0 &&
-                (a.N / a.nbparts) % W2T == 0;
+    // whole tiles and steps, 16-byte rows
+    bool ok = a.T % W2R == 0 && a.M % a.T == 0 && a.Ktot % W2T == 0 && (a.N / a.nbparts) % W2T == 0 && a.ldb % 8 == 0 &&
+              ((uintptr_t)(a.B16 ? (const void*)a.B16 : a.B) & 15) == 0;
     for (int p = 0; p < a.nparts; ++p) {
         const APart& q = a.A[p];
-        t128 = t128 && q.K % W2T == 0 && q.ld % 8 == 0 && ((uintptr_t)(q.p16 ? (const void*)q.p16 : q.ptr) & 15) == 0;
+        ok = ok && q.K % W2T == 0 && q.ld % 8 == 0 && ((uintptr_t)(q.p16 ? (const void*)q.p16 : q.ptr) & 15) == 0;
     }
-    t128 = t128 && a.ldb % 8 == 0 && ((uintptr_t)(a.B16 ? (const void*)a.B16 : a.B) & 15) == 0;
-    if (a.nbparts > 1 && !t128) return hipErrorInvalidValue;  // B parts: the tile kernel only
-    if (a.cpart && (!cdst || a.A[0].shift != 0 || (a.nparts > 1 && a.A[1].shift != 0))) return hipErrorInvalidValue;
-    if (!t128) a.cpart = nullptr;  // column sums by the separate kernels below
-    const int nchunks = (int)((a.M + a.rows_per_chunk - 1) / a.rows_per_chunk);
-    if (a.cpart && (int64_t)nchunks * a.Ktot > a.cpart_capacity) return hipErrorInvalidValue;
-    if (t128) {
-        const int64_t blocks = (int64_t)((nchunks + 7) / 8) * 8 * (a.Ktot / W2T) * (a.N / W2T);
-        hipLaunchKernelGGL(gemm_wgrad_t128_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
-    } else {
-        const int64_t blocks = (int64_t)((nchunks + 7) / 8) * 8 * (a.Ktot / GT) * (a.N / GT);
-        if (a.bf16) hipLaunchKernelGGL(gemm_wgrad_bf16_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(gemm_wgrad_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
-    }
+    if (!ok || (a.cpart && (!cdst || a.A[0].shift != 0 || (a.nparts > 1 && a.A[1].shift != 0)))) return hipErrorInvalidValue;
+    a.rows_per_chunk = wgrad_rows(a);
+    const int nchunks = (int)(a.M / a.rows_per_chunk);
+    if ((int64_t)nchunks * a.Ktot * a.N > a.part_capacity || (a.cpart && (int64_t)nchunks * a.Ktot > a.cpart_capacity))
+        return hipErrorInvalidValue;
+    const int64_t blocks = (int64_t)((nchunks + 7) / 8) * 8 * (a.Ktot / W2T) * (a.N / W2T);
+    if (a.bf16) hipLaunchKernelGGL(gemm_wgrad_t128_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(gemm_wgrad_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = reduce_parts(a.part, a.part_capacity, nchunks, (int64_t)a.Ktot * a.N, a.N, d, st);
     if (e != hipSuccess || !cdst) return e;
-    if (a.cpart) return reduce_parts(a.cpart, a.cpart_capacity, nchunks, a.Ktot, a.Ktot, *cdst, st);
-    // column sums part by part (each part's first column maps below or above the split as a whole)
-    for (int p = 0, kb = 0; p < a.nparts; kb += a.A[p].K, ++p) {
-        const APart& q = a.A[p];
-        float* base = kb < cdst->split ? cdst->d0 : cdst->d1;
-        if (!base) continue;
-        float* dst = kb < cdst->split ? base + kb * cdst->stride : base + (kb - cdst->split) * cdst->stride;
-        e = q.p16 ? colsum16(q.p16, q.ld, a.M, q.K, a.part, a.part_capacity, dst, cdst->stride, st)
-                  : colsum(q.ptr, q.ld, a.M, q.K, nullptr, 0, 0, a.part, a.part_capacity, dst, cdst->stride, st);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-hipError_t gemm_wgrad(const WgradArgs& a, float* dst, int out_mode, hipStream_t st) {
-    const int64_t KN = (int64_t)a.Ktot * a.N;
-    return gemm_wgrad(a, WgradDst{dst, nullptr, KN, (int64_t)(out_mode == 2 ? 2 : 1), false}, st);
+    return a.cpart ? reduce_parts(a.cpart, a.cpart_capacity, nchunks, a.Ktot, a.Ktot, *cdst, st) : hipErrorInvalidValue;
 }
 
 hipError_t colsum(const float* X, int64_t ldx, int64_t M, int N, const float* w, int64_t wstride, int relu,
                   float* part, int64_t part_capacity, float* dst, int64_t dst_stride, hipStream_t st) {
     if (N < 1 || part_capacity < N) return hipErrorInvalidValue;
     const bool vec = N % 4 == 0 && N <= 1024 && ldx % 4 == 0 && ((uintptr_t)X & 15) == 0;
+    if (!vec && (N != 1 || w || relu)) return hipErrorInvalidValue;
     // rows per chunk: enough chunks to fill the chip, partial sums within the buffer's capacity
     int64_t rpc = vec ? 512 : 4096;
     while (((M + rpc - 1) / rpc) * (int64_t)N > part_capacity) rpc *= 2;
@@ -1038,8 +966,7 @@ hipError_t colsum(const float* X, int64_t ldx, int64_t M, int N, const float* w,
     if (vec)
         hipLaunchKernelGGL(colsum4_kernel, dim3(nchunks), dim3(256), 0, st, X, ldx, M, N, w, wstride, relu, rpc, part);
     else
-        hipLaunchKernelGGL(colsum_kernel, dim3((N + 255) / 256, nchunks), dim3(256), 0, st, X, ldx, M, N, w, wstride,
-                           relu, rpc, part);
+        hipLaunchKernelGGL(colsum1_kernel, dim3(nchunks), dim3(256), 0, st, X, ldx, M, rpc, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return reduce_parts(part, part_capacity, nchunks, N, dst, dst_stride, st);
@@ -1048,22 +975,6 @@ hipError_t colsum(const float* X, int64_t ldx, int64_t M, int N, const float* w,
 hipError_t launch_input_proj(const float* u, int64_t M, const float* w_in, const float* b_in, float* x0,
                              hipStream_t st) {
     hipLaunchKernelGGL(input_proj_kernel, dim3(nblk(M * kC)), dim3(256), 0, st, u, M, w_in, b_in, x0);
-    return hipGetLastError();
-}
-hipError_t colsum16(const uint16_t* X, int64_t ldx, int64_t M, int N, float* part, int64_t part_capacity, float* dst,
-                    int64_t dst_stride, hipStream_t st) {
-    if (N < 4 || N % 4 || N > 1024 || ldx % 4 || ((uintptr_t)X & 7) || part_capacity < N) return hipErrorInvalidValue;
-    int64_t rpc = 512;
-    while (((M + rpc - 1) / rpc) * (int64_t)N > part_capacity) rpc *= 2;
-    const int nchunks = (int)((M + rpc - 1) / rpc);
-    hipLaunchKernelGGL(colsum16_kernel, dim3(nchunks), dim3(256), 0, st, X, ldx, M, N, rpc, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return reduce_parts(part, part_capacity, nchunks, N, dst, dst_stride, st);
-}
-
-hipError_t launch_gate_bwd(const float* pre, const float* dg, int64_t M, float* g, float* dpre, hipStream_t st) {
-    hipLaunchKernelGGL(gate_bwd_kernel, dim3(nblk(M * kC)), dim3(256), 0, st, pre, dg, M, g, dpre);
     return hipGetLastError();
 }
 hipError_t launch_head_bwd_elem(const float* h, const float* dz, int64_t M, const float* w2, int mid, float* dh,
