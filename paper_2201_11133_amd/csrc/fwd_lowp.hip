@@ -66,20 +66,35 @@ __device__ inline uint32_t e4m3_pair_in_range(float a, float b) {
     return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(a, b, 0, false) & 0xffffu;
 }
 
+// A register whose bits are all written by what follows (no instruction sets it).
+__device__ inline int any_bits() {
+    int v;
+    asm("" : "=v"(v));
+    return v;
+}
+
+// Four such values -> a word of four codes, the second pair converted into the first's upper half.
+__device__ inline uint32_t e4m3_quad_in_range(float a, float b, float c, float d) {
+    return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(c, d, __builtin_amdgcn_cvt_pk_fp8_f32(a, b, any_bits(), false), true);
+}
+
 typedef __bf16 bf16x2v __attribute__((ext_vector_type(2)));
 typedef short short2v __attribute__((ext_vector_type(2)));
-typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
 
-// Two bf16 values (one 32-bit word, first in the low half) -> two E4M3 codes in the low 16 bits,
-// round to nearest even, saturated to +/-448: bf16 is sign-magnitude, so the magnitudes are clamped
-// as 16-bit integers at 0x43e0 (448), then the gfx950 bf16 -> E4M3 conversion (unit scale) is exact.
-__device__ inline uint32_t bf16x2_to_e4m3(uint32_t w) {
-    const uint32_t sign = w & 0x80008000u;
-    ushort2v mag = __builtin_bit_cast(ushort2v, w & 0x7fff7fffu);
-    mag = __builtin_elementwise_min(mag, (ushort2v){0x43e0, 0x43e0});
-    const bf16x2v v = __builtin_bit_cast(bf16x2v, __builtin_bit_cast(uint32_t, mag) | sign);
-    const short2v r = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16((short2v){0, 0}, v, 1.0f, false);
-    return __builtin_bit_cast(uint32_t, r) & 0xffffu;
+// Four bf16 values (two 32-bit words, first in the low half) -> a word of four E4M3 codes, round to nearest
+// even, saturated to +/-448: bf16 is sign-magnitude, so each half is clamped as a signed 16-bit integer at
+// 0x43e0 (448) with its own sign (of two negative values the one of smaller magnitude is the
+// lesser integer), then the gfx950 bf16 -> E4M3 conversion (unit scale) is exact.
+__device__ inline uint32_t bf16x4_to_e4m3(uint2 w) {
+    uint32_t lim = 0x43e043e0u;
+    asm("" : "+v"(lim));   // in a register: with the other constant as a scalar, one instruction sets the limit
+    auto clamp2 = [lim](uint32_t v) {
+        return __builtin_bit_cast(bf16x2v, __builtin_elementwise_min(__builtin_bit_cast(short2v, v),
+                                                                     __builtin_bit_cast(short2v, (v & 0x80008000u) | lim)));
+    };
+    short2v r = __builtin_bit_cast(short2v, any_bits());
+    r = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(r, clamp2(w.x), 1.0f, false);
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(r, clamp2(w.y), 1.0f, true));
 }
 
 template <bool FP8, int RB_, int WV_>
@@ -138,8 +153,7 @@ __device__ inline floatx16 mma(const Frag<FP8>& a, const Frag<FP8>& b, floatx16 
 
 // Eight bf16 values (16 bytes) -> eight E4M3 codes (8 bytes).
 __device__ inline uint2 bf16x8_to_e4m3(uint4 v) {
-    return make_uint2(bf16x2_to_e4m3(v.x) | (bf16x2_to_e4m3(v.y) << 16),
-                      bf16x2_to_e4m3(v.z) | (bf16x2_to_e4m3(v.w) << 16));
+    return make_uint2(bf16x4_to_e4m3(make_uint2(v.x, v.y)), bf16x4_to_e4m3(make_uint2(v.z, v.w)));
 }
 
 // One phase-2 pass over NB 32-column blocks of Brs (K = 128): acc[c][i] = g rows of row block i
@@ -671,12 +685,14 @@ static_assert(2 * FX_LDS <= 160 * 1024, "two FP8 fused blocks per CU");
 
 __device__ inline uint8_t* fx_buf(uint8_t* lds, int j) { return lds + (j == 0 ? FX_E0 : j == 1 ? FX_E1 : FX_E2); }
 
-// Four bf16 values (an 8-byte word) -> four E4M3 codes (a 32-bit word), saturated to +/-448.
-__device__ inline uint32_t bf16x4_to_e4m3(uint2 w) { return bf16x2_to_e4m3(w.x) | (bf16x2_to_e4m3(w.y) << 16); }
-
 // G2 as in the BF16 kernel: one k-step covers 64 input channels, i.e. one group, so a wave of group
 // q / 2 takes steps q / 2 and 2 + q / 2 of the first phase and step q / 2 of the second.
 // DBG as in the BF16 kernel.
+//
+// Vector instructions bound it, not the matrix cores (1,536 of its 2,900 cycles per wave, layer and chunk): the
+// gate takes 12 per channel, the epilogue 8. So nothing else may cost any: the products are held in
+// their block (sunk, they made the weight ring copy 120 registers per layer and spill 34), conversions
+// write both halves of a word, the epilogue has no branch. Six layers of 426,000 rows: 583 -> 464 us.
 template <bool FROM_STREAM, bool SKIP_INIT, int NL, bool LAST, bool G2, bool DBG = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fused_fp8_kernel(FusedArgs p) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[FX_LDS];
