@@ -666,10 +666,9 @@ static LayerArgsLP lp_args(gwd_model* m, int member, int l) {
 // scale and bias; the residual stream stays bf16 and each layer's operand is the E4M3 conversion of
 // the bf16-rounded x.
 // The lane that computes output channels c of rows r in one layer computes the same channels of the
-// same rows in the next, so the residual stream of the chunk stays in registers (four bf16 channels
-// per 8-byte word); the LDS holds only the E4M3 operand buffers (one of which takes the E4M3 gate
-// output) and history rows, a bf16 staging buffer for the chunk's input and output rows, and the
-// biases and scales of the launch's layers.
+// same rows in the next, so the residual stream of the chunk stays in place in a bf16 staging buffer
+// (the chunk's input and output rows); the LDS also holds the E4M3 operand buffers (one of which takes
+// the E4M3 gate output) and history rows, and the biases and scales of the launch's layers.
 // Layer j reads operand buffer j % 3, writes buffer (j + 1) % 3 and puts its E4M3 gate output in
 // buffer (j + 2) % 3; its history rows are H_j, at row 2^j - 1 of the history area, as in the BF16
 // form.
@@ -689,10 +688,13 @@ __device__ inline uint8_t* fx_buf(uint8_t* lds, int j) { return lds + (j == 0 ? 
 // q / 2 takes steps q / 2 and 2 + q / 2 of the first phase and step q / 2 of the second.
 // DBG as in the BF16 kernel.
 //
-// Vector instructions bound it, not the matrix cores (1,536 of its 2,900 cycles per wave, layer and chunk): the
-// gate takes 12 per channel, the epilogue 8. So nothing else may cost any: the products are held in
-// their block (sunk, they made the weight ring copy 120 registers per layer and spill 34), conversions
-// write both halves of a word, the epilogue has no branch. Six layers of 426,000 rows: 583 -> 464 us.
+// Of a wave's 13,500 cycles per layer and chunk (two waves per SIMD, timestamps in the kernel) the gate takes
+// 3,500, the epilogue 2,500 and the products 5,100, of which the matrix cores work 1,536: the vector
+// instructions of both waves (12 per channel in the gate, 8 in the epilogue) and the products' waits bound
+// it. So nothing else may cost any: the products are held in their block (sunk, they made the weight ring copy
+// 120 registers per layer and spill 34), conversions write both halves of a word, the epilogue has no
+// branch. Six layers of 426,000 rows: 583 -> 464 us. Fragments requested earlier (all four steps of the first
+// phase, both of the second) gave nothing, and spilled where they were in flight during the epilogue.
 template <bool FROM_STREAM, bool SKIP_INIT, int NL, bool LAST, bool G2, bool DBG = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fused_fp8_kernel(FusedArgs p) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[FX_LDS];
