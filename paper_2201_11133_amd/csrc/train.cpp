@@ -133,8 +133,8 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
     BlobOffsets v = blob_offsets(m->arch);
     const float* w = (const float*)m->canon[member];
     // weight-gradient partials: one chunk per window, or split windows (gemm_wgrad: at most 1,023 output
-    // tiles of 128 x 128 then, the 256 products of 2C x 2C this leaves room for)
-    const int64_t nch = std::max<int64_t>(B, 256);
+    // tiles of 128 x 128 or 383 of 256 x 256 then)
+    const int64_t nch = std::max<int64_t>(B, 384);
     // workspace (floats): XS[LPS][M][128] PRE[LPS][M][256] G DG DX DSKIP SKS R H DH AH [M][128] each, partials
     const int64_t f_xs = 0, f_pre = f_xs + (int64_t)LPS * M * kC, f_g = f_pre + (int64_t)LPS * M * 2 * kC;
     const int64_t f_dg = f_g + M * kC, f_dx = f_dg + M * kC, f_ds = f_dx + M * kC, f_sks = f_ds + M * kC;

@@ -421,6 +421,21 @@ __device__ inline u32x4 w2_bf16x8(u32x4 lo, u32x4 hi) {  // 8 fp32 (raw bits) ->
     return __builtin_bit_cast(u32x4, bf16_pack8(__builtin_bit_cast(float4, lo), __builtin_bit_cast(float4, hi)));
 }
 
+// Eight rows of 8 bf16 columns -> 8 columns of 8 rows, as 16-byte words of the LDS tile.
+__device__ inline void w2_store_columns(const u32x4 (&w)[8], uint8_t* dst) {
+    // column c: rows (2q, 2q + 1) as one bf16 pair, q < 4
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        u32x4 o;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t lo = w[2 * q][c >> 1], hi = w[2 * q + 1][c >> 1];
+            o[q] = (c & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
+        }
+        *(u32x4*)(dst + c * W2LD) = o;
+    }
+}
+
 __global__ __launch_bounds__(256) void gemm_wgrad_t128_kernel(WgradArgs a) {
     __shared__ __attribute__((aligned(16))) uint8_t lds[2 * 2 * W2OP];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -486,17 +501,7 @@ __global__ __launch_bounds__(256) void gemm_wgrad_t128_kernel(WgradArgs a) {
                                   : __uint_as_float(raw[2 * j + (c >> 2)][c & 3]);
             }
         }
-        // column c: rows (2q, 2q + 1) as one bf16 pair, q < 4
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            u32x4 o;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t lo = w[2 * q][c >> 1], hi = w[2 * q + 1][c >> 1];
-                o[q] = (c & 1) ? ((lo >> 16) | (hi & 0xffff0000u)) : ((lo & 0xffffu) | (hi << 16));
-            }
-            *(u32x4*)(dst + (8 * cm + c) * W2LD + 16 * rg) = o;
-        }
+        w2_store_columns(w, dst + 8 * cm * W2LD + 16 * rg);
     };
     floatx16 acc[2][2] = {};
     u32x4 raw[16];
@@ -545,6 +550,94 @@ __global__ __launch_bounds__(256) void gemm_wgrad_t128_kernel(WgradArgs a) {
         }
         if (rg == 0) {
             float* o = a.cpart + (int64_t)chunk * a.Ktot + k0 + 8 * cm;
+            *(float4*)o = make_float4(cs[0], cs[1], cs[2], cs[3]);
+            *(float4*)(o + 4) = make_float4(cs[4], cs[5], cs[6], cs[7]);
+        }
+    }
+}
+
+// The 256 x 256 product of bf16 rows (the conv taps' gradient: A one part, B two) as one tile per block of eight
+// waves: waves 0-3 stage A, waves 4-7 B, wave (wk, wn) owns output rows 128 wk .. + 128 and columns
+// 64 wn .. + 64, everything else as above. What bounds the 128 x 128 tiles is the rows in flight between
+// the caches and the CUs (64 KB per CU): four blocks of a chunk read every row twice. 524,288 rows: 167 us
+// there, 126 us here with one block per CU; the bytes alone take 81 us at the rate of a copy.
+constexpr int W3T = 256;
+__global__ __launch_bounds__(512) void gemm_wgrad_t256_kernel(WgradArgs a) {
+    __shared__ __attribute__((aligned(16))) uint8_t lds[2 * 2 * W3T * W2LD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wk = wave & 1, wn = wave >> 1, h = lane >> 5, r = lane & 31;
+    const int chunk = blockIdx.x;
+    const int64_t r0 = (int64_t)chunk * a.rows_per_chunk;
+    const bool isA = wave < 4;
+    const int t2 = tid & 255, rg = t2 & 7, cm = t2 >> 3;   // rows 8 rg .. + 8, columns 8 cm .. + 8
+    const int second = !isA && cm >= 16;                   // B's second part: the same columns, shifted
+    const uint16_t* src = isA ? a.A[0].p16 + 8 * cm : a.B16 + 8 * (cm & 15);
+    const int64_t ld = isA ? a.A[0].ld : a.ldb;
+    const int shift = isA ? 0 : second ? a.bshift1 : a.bshift;
+    const bool csum = a.cpart != nullptr && isA;           // uniform per wave
+    float cs[8] = {};
+    const int tb = (int)(r0 % a.T);                        // the chunk's first time step and window
+    const int64_t wrow0 = r0 - tb;
+    u32x4 raw[8];
+    auto load = [&](int step) __attribute__((always_inline)) {   // (rows outside the window read the unshifted row)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int t = tb + step * W2R + 8 * rg + j;
+            raw[j] = *(const u32x4*)(src + (wrow0 + t + ((unsigned)(t + shift) < (unsigned)a.T ? shift : 0)) * ld);
+        }
+    };
+    floatx16 acc[4][2] = {};
+    const int nsteps = (int)(a.rows_per_chunk / W2R);
+    load(0);
+    for (int s = 0; s < nsteps; ++s) {
+        uint8_t* At = lds + (s & 1) * 2 * W3T * W2LD;
+        uint8_t* Bt = At + W3T * W2LD;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int t = tb + s * W2R + 8 * rg + j;
+            if ((unsigned)(t + shift) >= (unsigned)a.T) raw[j] = u32x4{0, 0, 0, 0};
+            if (csum) {
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    cs[c] += __uint_as_float((c & 1) ? (raw[j][c >> 1] & 0xffff0000u) : (raw[j][c >> 1] << 16));
+            }
+        }
+        w2_store_columns(raw, (isA ? At : Bt) + 8 * cm * W2LD + 16 * rg);
+        __syncthreads();
+        if (s + 1 < nsteps) load(s + 1);   // in flight during the products
+#pragma unroll
+        for (int s16 = 0; s16 < W2R / 16; ++s16) {
+            bf16x8 av[4], bv[2];
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                av[i] = *(const bf16x8*)(At + (128 * wk + 32 * i + r) * W2LD + 2 * (16 * s16 + 8 * h));
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+                bv[c] = *(const bf16x8*)(Bt + (64 * wn + 32 * c + r) * W2LD + 2 * (16 * s16 + 8 * h));
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int c = 0; c < 2; ++c)
+                    acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[i], bv[c], acc[i][c], 0, 0, 0);
+        }
+    }
+    float* out = a.part + (int64_t)chunk * W3T * W3T;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                out[(128 * wk + 32 * i + 8 * (e >> 2) + 4 * h + (e & 3)) * W3T + 64 * wn + 32 * c + r] = acc[i][c][e];
+    if (csum) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            cs[c] += __shfl_xor(cs[c], 1);
+            cs[c] += __shfl_xor(cs[c], 2);
+            cs[c] += __shfl_xor(cs[c], 4);
+        }
+        if (rg == 0) {
+            float* o = a.cpart + (int64_t)chunk * W3T + 8 * cm;
             *(float4*)o = make_float4(cs[0], cs[1], cs[2], cs[3]);
             *(float4*)(o + 4) = make_float4(cs[4], cs[5], cs[6], cs[7]);
         }
@@ -921,10 +1014,9 @@ hipError_t gemm_rows(const GemmRowsArgs& a, hipStream_t st) {
 // Rows per chunk: whole windows when they give a block for each of the chip's 512 slots (two per CU), else
 // windows halved, down to 128 rows (two steps of the bf16 kernel). 8 windows of 4,096 rows have 8 chunks
 // otherwise, 32 blocks or fewer; 128 windows the same 512 blocks for the conv taps, but 256 for skip and residual.
-static int64_t wgrad_rows(const WgradArgs& a) {
-    const int64_t tiles = (int64_t)(a.Ktot / W2T) * (a.N / W2T);
+static int64_t wgrad_rows(const WgradArgs& a, int64_t tiles, int64_t blocks) {
     int64_t rpc = a.T;
-    while ((a.M / rpc) * tiles < 512 && rpc % 256 == 0) rpc /= 2;
+    while ((a.M / rpc) * tiles < blocks && rpc % 256 == 0) rpc /= 2;
     return rpc;
 }
 
@@ -940,12 +1032,22 @@ hipError_t gemm_wgrad(const WgradArgs& a0, const WgradDst& d, hipStream_t st, co
         ok = ok && q.K % W2T == 0 && q.ld % 8 == 0 && ((uintptr_t)(q.p16 ? (const void*)q.p16 : q.ptr) & 15) == 0;
     }
     if (!ok || (a.cpart && (!cdst || a.A[0].shift != 0 || (a.nparts > 1 && a.A[1].shift != 0)))) return hipErrorInvalidValue;
-    a.rows_per_chunk = wgrad_rows(a);
+    a.rows_per_chunk = wgrad_rows(a, (a.Ktot / W2T) * (a.N / W2T), 512);
+    // the 256 x 256 tile: enough chunks for three quarters of the CUs, long enough (16 steps) to be worth their
+    // partial sums of 256 KB each (128 windows of 4,096: 33 MB more, 4 us of reduction for the 41 us gained)
+    bool t256 = a.bf16 && a.nparts == 1 && a.Ktot == W3T && a.N == W3T && a.nbparts == 2 && a.A[0].p16 && a.B16 &&
+                a.A[0].shift == 0;
+    if (t256) {
+        const int64_t rpc = wgrad_rows(a, 1, 192);
+        t256 = rpc >= 1024 && a.M / rpc >= 192;
+        if (t256) a.rows_per_chunk = rpc;
+    }
     const int nchunks = (int)(a.M / a.rows_per_chunk);
     if ((int64_t)nchunks * a.Ktot * a.N > a.part_capacity || (a.cpart && (int64_t)nchunks * a.Ktot > a.cpart_capacity))
         return hipErrorInvalidValue;
     const int64_t blocks = (int64_t)((nchunks + 7) / 8) * 8 * (a.Ktot / W2T) * (a.N / W2T);
-    if (a.bf16) hipLaunchKernelGGL(gemm_wgrad_t128_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
+    if (t256) hipLaunchKernelGGL(gemm_wgrad_t256_kernel, dim3((unsigned)nchunks), dim3(512), 0, st, a);
+    else if (a.bf16) hipLaunchKernelGGL(gemm_wgrad_t128_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
     else hipLaunchKernelGGL(gemm_wgrad_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -11,7 +11,7 @@ torch = pytest.importorskip("torch")
 
 @pytest.mark.parametrize("prec", ["fp32", "bf16"])
 @pytest.mark.parametrize("B,T,layer", [(1, 128, 29), (1, 384, 7), (3, 256, 8), (5, 640, 28), (2, 2048, 9), (65, 1024, 19),
-                                       (513, 128, 3)])
+                                       (513, 128, 3), (192, 1024, 9), (97, 2048, 28), (201, 1152, 5)])
 def test_products_of_one_layer(prec, B, T, layer):
     """One layer's products in float64 from the operands its kernels read, within the forward-error bound
     of a dot product of length K, K u (|A| |B|), K the contraction length of the row products and the rows of the
