@@ -181,17 +181,29 @@ gwd_status check_forward(const gwd_model* m, const gwd_stream* streams, int32_t 
 // row goes through the same operations wherever it sits in a window. Windows of 4096 at stride 256
 // compute each row 16 times over; here each stream becomes one window, or windows that overlap by the
 // receptive field only. A single stream is split evenly into windows of at most one batch of rows
-// (batch_windows x window, so the workspace is never larger than the request's own windows need);
+// (batch_windows x window, so the workspace is never larger than the request's own windows need, and no
+// more than the device memory allows);
 // several streams share a batch, with windows of at most an eighth of it, and each window stops at its
 // stream's end (FwdBatch::rows). Scores are bit for bit those of the request's own windows. Windows
 // 4096 / 256, four members in BF16: 8 s of strain 15.1 -> 1.94 ms (1.20 ms with the members in one launch),
 // 256 s 459 -> 31.3 ms; one FP32 member, 16 s: 84.6 -> 6.03 ms.
+constexpr int64_t kRowBytes = 3 * kC * 4;      // workspace per row: x ping-pong and skip
+constexpr int64_t kMostRows = 1 << 22;         // rows that a merged window or a group of members may take together
+
+// Bytes that the activations may take: 60 % of the device memory free now, with what the model holds.
+static int64_t allowed_bytes(const gwd_model* m) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) return INT64_MAX;
+    return (int64_t)((double)(free_b + (size_t)m->ws.bytes) * 0.6);
+}
+
 static bool merged_windows(const gwd_model* m, const gwd_stream* streams, int n_streams, int64_t total_win, int& window,
                            int& stride) {
     const int64_t H = (rf_of(&m->arch) - 1 + 127) / 128 * 128;   // overlap: whole 128-row tiles
     int64_t longest = 0;
     for (int s = 0; s < n_streams; ++s) longest = std::max<int64_t>(longest, streams[s].length);
-    const int64_t batch = std::min<int64_t>((int64_t)m->batch_windows * window, 1 << 22);
+    int64_t batch = std::min<int64_t>((int64_t)m->batch_windows * window, kMostRows);
+    if (std::min(batch, longest) * kRowBytes > m->ws.bytes) batch = std::min(batch, allowed_bytes(m) / kRowBytes);
     const int64_t cap = std::max<int64_t>(window, (n_streams == 1 ? batch : batch / 8) / 128 * 128);
     int64_t W = (longest + 127) / 128 * 128, S = W;
     if (W > cap) {
@@ -293,16 +305,23 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
             for (int64_t k = 0; k < nwin[i]; ++k)
                 rows.push_back((int32_t)std::min<int64_t>(window, streams[i].length - k * stride));
     nb_max = (int)std::min<int64_t>(merged ? std::max<int64_t>(1, batch_rows / window) : m->batch_windows, total_win);
+    // as many members per launch as fit a batch of rows: a small request's launches would leave most of
+    // the chip idle, or run each block for one chunk beside a warm-up chunk. Four members: BF16, 8 s
+    // 1.98 -> 1.20 ms, five ragged FP8 streams of 22 s 5.94 -> 2.98 ms, two-branch, 32 s 3.25 -> 2.85 ms;
+    // 256 s (two members per launch) 31.3 ms either way
+    fb.n_group = 1;
+    if (m->arch.kind == 1 && !persist) {
+        const int64_t fit = std::min(batch_rows, kMostRows) / ((int64_t)nb_max * window);
+        fb.n_group = member_group(m, (int)std::max<int64_t>(1, std::min<int64_t>(m->n_members, fit)));
+    }
     if (m->arch.kind == 1) {
-        // long windows: cap the windows per batch so the activations (x ping-pong and skip, 3 x 512 B
-        // per time step) stay within 60 % of the device memory free now (plus what the model holds)
-        const int64_t per_window = (int64_t)window * kC * 4 * 3;
-        if ((int64_t)nb_max * per_window > m->ws.bytes) {
-            size_t free_b = 0, total_b = 0;
-            if (hipMemGetInfo(&free_b, &total_b) == hipSuccess) {
-                const int64_t allowed = (int64_t)((double)(free_b + (size_t)m->ws.bytes) * 0.6);
-                nb_max = (int)std::max<int64_t>(1, std::min<int64_t>(nb_max, allowed / per_window));
-            }
+        // long windows: cap the windows per batch (and the members per launch) so the activations stay
+        // within the memory they may take
+        const int64_t per_window = (int64_t)window * kRowBytes;
+        if ((int64_t)nb_max * fb.n_group * per_window > m->ws.bytes) {
+            const int64_t allowed = allowed_bytes(m);
+            nb_max = (int)std::max<int64_t>(1, std::min<int64_t>(nb_max, allowed / per_window));
+            fb.n_group = (int)std::max<int64_t>(1, std::min<int64_t>(fb.n_group, allowed / (nb_max * per_window)));
         }
     }
     // workspace: stream table (sized for the largest table so far; then the persistent launch's
@@ -313,13 +332,7 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
     const int64_t stream_bytes = (desc_bytes + first_bytes + row_bytes + 255) & ~255LL;
     const int64_t persist_bytes = persist ? persistent_table_bytes(m, window) : 0;
     const int64_t tab_bytes = std::max<int64_t>(m->ws_tab_bytes, stream_bytes + persist_bytes);
-    // as many members per launch as fit a batch of rows: a small request's launches would leave most of
-    // the chip idle, or run each block for one chunk beside a warm-up chunk. Four members: BF16, 8 s
-    // 1.98 -> 1.20 ms, five ragged FP8 streams of 22 s 5.94 -> 2.98 ms, two-branch, 32 s 3.25 -> 2.85 ms;
-    // 256 s (two members per launch) 31.3 ms either way
     const int64_t rows_batch = (int64_t)nb_max * window;
-    fb.n_group = persist || m->arch.kind != 1
-                     ? 1 : member_group(m, (int)std::max<int64_t>(1, std::min<int64_t>(m->n_members, batch_rows / rows_batch)));
     fb.act_stride = rows_batch * kC;
     int64_t act_bytes = m->arch.kind == 1 ? 3 * fb.n_group * fb.act_stride * 4 : 0;
     if (persist) {  // two blocks per compute unit (at most one per window), each holding up to

@@ -68,3 +68,35 @@ def test_members_of_one_launch(g, prec, members):
         assert torch.equal(w[i], one.forward(xs[:1], 4096, 1024, 2))
         one.close()
     assert torch.equal(e[:n], e[n:].reshape(members, n).min(dim=0).values)
+
+
+@pytest.mark.parametrize("seconds,merging", [(64, True), (400, True), (400, False)])
+def test_little_free_memory(seconds, merging):
+    """With 4 GiB of device memory free, a request whose windows and members would not fit together is split
+    further, with the same scores."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2201_11133_amd import gwd, synth
+    print(f"case: {seconds} s, merging {merging}", flush=True)
+    blobs = np.stack([synth.full_weights(i) for i in range(4)])
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((seconds * 4096, 2), generator=gen, device="cuda")
+    window, stride = (4096, 256) if merging else (1 << 18, (1 << 18) - 3072)
+    want = gwd.Model(gwd.full_arch(), blobs, "bf16")
+    want.set_window_merging(merging)
+    ref = want.forward([x], window, stride).clone()
+    want.close()
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    m = gwd.Model(gwd.full_arch(), blobs, "bf16")
+    m.set_window_merging(merging)
+    free, _ = torch.cuda.mem_get_info()
+    ballast = torch.empty(free - (4 << 30), dtype=torch.uint8, device="cuda")
+    try:
+        got = m.forward([x], window, stride)
+        torch.cuda.synchronize()
+        assert torch.equal(got, ref)
+    finally:
+        del ballast
+        torch.cuda.empty_cache()
+        m.close()
