@@ -432,6 +432,7 @@ void gwd_plan_free(gwd_plan* plan);
  *     at any window length; 1 = one launch per layer; 0 = default (6 where
  *     sextets apply, else 3); FP32 models accept 0 or 1;
  *   batch_windows: windows per batch of layer launches (1..8192, default 512;
+ *     merged windows, gwd_set_window_merging, take as many rows at most;
  *     gwd_forward lowers it for a call whose activations would not fit in 60 %
  *     of the free device memory, e.g. windows of 2^20 samples).
  * Results do not depend on any of them. GWD_ERR_ARG for other values. */
@@ -472,7 +473,8 @@ gwd_status gwd_set_persistent(gwd_model* model, int32_t on);
  * stream as one window, or as windows that overlap by the receptive field
  * only, and compute no row twice that the scores do not need twice. The
  * scores are bit for bit those of the request's own windows, and the
- * workspace is no larger. on = 0 runs every row of every window of the request, as an engine that maps
+ * workspace stays within that of one batch of them (batch_windows x window
+ * rows; a small request may take several members' rows of it at once). on = 0 runs every row of every window of the request, as an engine that maps
  * windows to windows does ("Optimization with TensorRT"). out_mode 2, the
  * small member and the persistent forward always do. GWD_ERR_ARG unless on is
  * 0 or 1. */
