@@ -77,10 +77,14 @@ static gwd_status fwd_train_kind1(gwd_model* m, int member, const float* u, int 
     if (m->prec == GWD_BF16 || m->prec == GWD_FP8_E4M3) {
         // bf16 residual stream, as in the inference forward: the saved stack inputs are bf16 (each
         // in the first half of its slot), the input projection is rounded to bf16 once
-        e = launch_input_proj(u, M, w + v.in_w, w + v.in_b, xa, st);
+        if (((uintptr_t)saved & 7) == 0) {
+            e = launch_input_proj_bf16(u, M, w + v.in_w, w + v.in_b, (uint16_t*)saved, st);
+        } else {   // (8-byte stores need the alignment)
+            e = launch_input_proj(u, M, w + v.in_w, w + v.in_b, xa, st);
+            if (e != hipSuccess) return hip_fail(e, "input projection");
+            e = launch_f32_to_bf16(xa, M * kC, (uint16_t*)saved, st);
+        }
         if (e != hipSuccess) return hip_fail(e, "input projection");
-        e = launch_f32_to_bf16(xa, M * kC, (uint16_t*)saved, st);
-        if (e != hipSuccess) return hip_fail(e, "bf16 rounding");
         // fused launches as in the inference forward (a stack ends on a launch boundary)
         const uint16_t* xin = (const uint16_t*)saved;
         uint16_t *ya = (uint16_t*)xa, *yb = (uint16_t*)xb;
@@ -110,10 +114,14 @@ static gwd_status fwd_train_kind1(gwd_model* m, int member, const float* u, int 
         }
     }
     // head: h = W_h1 ReLU(skip) + b_h1; logit = w_h2 . act(h) + b_h2
-    e = launch_relu_copy(skip, M * kC, R, st);
-    if (e != hipSuccess) return hip_fail(e, "relu");
+    const bool direct = ((uintptr_t)skip & 15) == 0;   // the product reads 16-byte words: ReLU there, else in a copy
+    if (!direct) {
+        e = launch_relu_copy(skip, M * kC, R, st);
+        if (e != hipSuccess) return hip_fail(e, "relu");
+    }
     GemmRowsArgs g{};
-    g.A[0] = APart{R, kC, 0, kC};
+    g.A[0] = APart{direct ? skip : R, kC, 0, kC};
+    g.relu_a = direct;
     g.B[0] = BPart{w + v.h1w, 1, kC};  // B(k = c, n = j) = h1.W[j][c]
     g.nparts = 1; g.M = M; g.N = kC; g.T = T; g.C = H; g.ldc = kC; g.bias = w + v.h1b;
     g.btf = fptr(m->tws.base, 4 * M * kC);
@@ -181,19 +189,19 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
         const WgradDst cd{grad + v.h1b, nullptr, kC, 1, false};
         HIPCHK(gemm_wgrad(a, WgradDst{grad + v.h1w, nullptr, (int64_t)kC * kC, 1, false}, st, &cd), "d h1.W, d h1.b");
     }
+    // BF16/FP8 members: dskip also rounded to bf16 once, in R (free after the products above); its GEMMs
+    // would round it on every read
+    uint16_t* DS16 = BT ? (uint16_t*)R : nullptr;
     {
         GemmRowsArgs g{};
         g.A[0] = APart{DH, kC, 0, kC};
         g.B[0] = BPart{w + v.h1w, kC, 1};      // B(k = j, n = c) = h1.W[j][c]
+        g.c16 = DS16;
         g.nparts = 1; g.M = M; g.N = kC; g.T = T; g.C = DS; g.ldc = kC; g.mask = skip; g.ldm = kC;
         g.bt = BT; g.btf = fptr(b, f_bt);
         HIPCHK(gemm_rows(g, st), "dskip");
     }
     HIPCHK(launch_fill(DX, M * kC, 0.f, st), "zero dx");
-    // BF16/FP8 members: dskip rounded to bf16 once, in R (free after the head); its GEMMs would
-    // round it on every read
-    uint16_t* DS16 = BT ? (uint16_t*)R : nullptr;
-    if (BT) HIPCHK(launch_f32_to_bf16(DS, M * kC, DS16, st), "dskip bf16");
     // ---- stacks, last to first
     for (int sidx = m->arch.n_stacks - 1; sidx >= 0; --sidx) {
         // recompute the stack, keeping each layer's input and pre-activation

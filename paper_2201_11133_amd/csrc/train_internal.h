@@ -44,6 +44,8 @@ struct GemmRowsArgs {
     const float* gpre32;
     float* g32;
     float* dpre32;
+    bool relu_a;         // A is max(A, 0) (fp32 form)
+    uint16_t* c16;       // optional: C also rounded to bf16 (same rows)
 };
 
 struct WgradArgs {
@@ -94,6 +96,8 @@ hipError_t colsum(const float* X, int64_t ldx, int64_t M, int N, const float* w,
                   float* part, int64_t part_capacity, float* dst, int64_t dst_stride, hipStream_t st);
 hipError_t launch_input_proj(const float* u, int64_t M, const float* w_in, const float* b_in, float* x0,
                              hipStream_t st);
+hipError_t launch_input_proj_bf16(const float* u, int64_t M, const float* w_in, const float* b_in, uint16_t* x0,
+                                  hipStream_t st);
 hipError_t launch_head_bwd_elem(const float* h, const float* dz, int64_t M, const float* w2, int mid, float* dh,
                                 float* ah, hipStream_t st);
 hipError_t launch_head_logit(const float* h, int64_t M, const float* w2, const float* b2, int mid, float* z,

@@ -179,6 +179,9 @@ __device__ __forceinline__ void rows_epilogue(const GemmRowsArgs& a, const float
                 if (a.mask) v[j] = (m4[j] > 0.f) ? v[j] : 0.f;
             }
             *(float4*)(a.C + (rbase + 8 * it) * a.ldc + n4) = make_float4(v[0], v[1], v[2], v[3]);
+            if (a.c16)
+                *(u32x2*)(a.c16 + (rbase + 8 * it) * a.ldc + n4) =
+                    bf16_pack4(u32x4{__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]), __float_as_uint(v[3])});
         }
     }
 }
@@ -316,7 +319,7 @@ __global__ __launch_bounds__(256) void pack_btf_kernel(GemmRowsArgs a, int Ktot)
     a.btf[f] = bp.ptr[(int64_t)k * bp.ld + (int64_t)n * bp.es];
 }
 
-template <int RB>
+template <int RB, bool RELU>
 __global__ __launch_bounds__(256) void gemm_rows_f32_kernel(GemmRowsArgs a, int Ktot) {
     __shared__ __attribute__((aligned(16))) float smem[64 * EP];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -355,6 +358,10 @@ __global__ __launch_bounds__(256) void gemm_rows_f32_kernel(GemmRowsArgs a, int 
             for (int c = 0; c < 2; ++c) bf[g][c] = *(const float4*)(bfr + c * ctile + (int64_t)(4 * ci + g) * 64 * 4);
         __syncthreads();  // the previous chunk's operands are read
         const int sh = a.A[ci < n0 ? 0 : 1].shift;
+        if (RELU)   // (a.relu_a; tested in the loop it cost an FP32 pass 0.3 %)
+#pragma unroll
+            for (int i = 0; i < 2 * RB; ++i)
+                raw[i] = make_float4(fmaxf(raw[i].x, 0.f), fmaxf(raw[i].y, 0.f), fmaxf(raw[i].z, 0.f), fmaxf(raw[i].w, 0.f));
 #pragma unroll
         for (int i = 0; i < 2 * RB; ++i) {
             const bool ok = row_ok(sh, i);
@@ -902,6 +909,20 @@ __global__ __launch_bounds__(256) void input_grad_kernel(const float* dx0, int64
     du[2 * row + 1] = s1;
 }
 
+// The same rounded to bf16, for the bf16 residual stream: four channels per thread, 8-byte stores (524,288 rows: a
+// pass in fp32 and one to round it took 274 us).
+__global__ __launch_bounds__(256) void input_proj_bf16_kernel(const float* u, int64_t M, const float* w_in, const float* b_in,
+                                                              uint16_t* x0) {
+    const int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x);
+    if (i >= M * kC) return;
+    const int64_t row = i / kC;
+    const int c = (int)(i % kC);
+    const float u0 = u[2 * row], u1 = u[2 * row + 1];
+    u32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(b_in[c + e] + w_in[2 * (c + e)] * u0 + w_in[2 * (c + e) + 1] * u1);
+    *(u32x2*)(x0 + i) = bf16_pack4(v);
+}
 __global__ __launch_bounds__(256) void relu_copy_kernel(const float* x, int64_t n, float* y) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) y[i] = fmaxf(x[i], 0.f);
@@ -998,6 +1019,7 @@ hipError_t gemm_rows(const GemmRowsArgs& a, hipStream_t st) {
          (!a.bias || ((uintptr_t)a.bias & 15) == 0);
     if (!ok || (!bf16 && (any16 || !a.btf))) return hipErrorInvalidValue;
     if (!a.C && !a.gpre && !a.gpre32) return hipErrorInvalidValue;
+    if ((a.relu_a && bf16) || (a.c16 && (!a.C || a.gpre || a.gpre32 || ((uintptr_t)a.c16 & 7)))) return hipErrorInvalidValue;
     if ((a.gpre || a.gpre32) && (a.N != kC || a.bias || a.beta != 0.f || a.mask)) return hipErrorInvalidValue;
     if (a.gpre && (!bf16 || !a.g16 || !a.dpre16 || ((uintptr_t)a.gpre & 7))) return hipErrorInvalidValue;
     if (a.gpre32 && (!a.g32 || !a.dpre32 || (((uintptr_t)a.gpre32 | (uintptr_t)a.g32 | (uintptr_t)a.dpre32) & 15)))
@@ -1006,8 +1028,14 @@ hipError_t gemm_rows(const GemmRowsArgs& a, hipStream_t st) {
     if (bf16) hipLaunchKernelGGL(pack_bt_kernel, pgrid, dim3(256), 0, st, a, Ktot);
     else hipLaunchKernelGGL(pack_btf_kernel, pgrid, dim3(256), 0, st, a, Ktot);
     if (bf16) hipLaunchKernelGGL(gemm_rows_bf16_kernel, grid, dim3(256), 0, st, a, Ktot);
-    else if (grid.x >= 512) hipLaunchKernelGGL(gemm_rows_f32_kernel<2>, grid, dim3(256), 0, st, a, Ktot);
-    else hipLaunchKernelGGL(gemm_rows_f32_kernel<1>, dim3(2 * grid.x), dim3(256), 0, st, a, Ktot);
+    else if (grid.x >= 512) {
+        if (a.relu_a) hipLaunchKernelGGL((gemm_rows_f32_kernel<2, true>), grid, dim3(256), 0, st, a, Ktot);
+        else hipLaunchKernelGGL((gemm_rows_f32_kernel<2, false>), grid, dim3(256), 0, st, a, Ktot);
+    } else {
+        const dim3 grid1(2 * grid.x);
+        if (a.relu_a) hipLaunchKernelGGL((gemm_rows_f32_kernel<1, true>), grid1, dim3(256), 0, st, a, Ktot);
+        else hipLaunchKernelGGL((gemm_rows_f32_kernel<1, false>), grid1, dim3(256), 0, st, a, Ktot);
+    }
     return hipGetLastError();
 }
 
@@ -1091,6 +1119,11 @@ hipError_t launch_head_logit(const float* h, int64_t M, const float* w2, const f
 }
 hipError_t launch_input_grad(const float* dx0, int64_t M, const float* w_in, float* du, hipStream_t st) {
     hipLaunchKernelGGL(input_grad_kernel, dim3(nblk(M)), dim3(256), 0, st, dx0, M, w_in, du);
+    return hipGetLastError();
+}
+hipError_t launch_input_proj_bf16(const float* u, int64_t M, const float* w_in, const float* b_in, uint16_t* x0,
+                                  hipStream_t st) {
+    hipLaunchKernelGGL(input_proj_bf16_kernel, dim3(nblk(M * kC / 4)), dim3(256), 0, st, u, M, w_in, b_in, x0);
     return hipGetLastError();
 }
 hipError_t launch_relu_copy(const float* x, int64_t n, float* y, hipStream_t st) {
