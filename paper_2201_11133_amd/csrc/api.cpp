@@ -183,10 +183,10 @@ gwd_status check_forward(const gwd_model* m, const gwd_stream* streams, int32_t 
 // receptive field only. A single stream is split evenly into windows of at most one batch of rows
 // (batch_windows x window, so the workspace is never larger than the request's own windows need, and no
 // more than the device memory allows);
-// several streams share a batch, with windows of at most an eighth of it, and each window stops at its
-// stream's end (FwdBatch::rows). Scores are bit for bit those of the request's own windows. Windows
-// 4096 / 256, four members in BF16: 8 s of strain 15.1 -> 1.94 ms (1.20 ms with the members in one launch),
-// 256 s 459 -> 31.3 ms; one FP32 member, 16 s: 84.6 -> 6.03 ms.
+// several streams share a batch, with windows of an eighth of it or less (merged_windows takes the cheapest),
+// and each window stops at its stream's end (FwdBatch::rows). Scores are bit for bit those of the request's
+// own windows. Windows 4096 / 256, four members in BF16: 8 s of strain 15.1 -> 1.94 ms (1.20 ms with the
+// members in one launch), 256 s 459 -> 31.3 ms; one FP32 member, 16 s: 84.6 -> 6.03 ms.
 constexpr int64_t kRowBytes = 3 * kC * 4;      // workspace per row: x ping-pong and skip
 constexpr int64_t kMostRows = 1 << 22;         // rows that a merged window or a group of members may take together
 
@@ -197,30 +197,68 @@ static int64_t allowed_bytes(const gwd_model* m) {
     return (int64_t)((double)(free_b + (size_t)m->ws.bytes) * 0.6);
 }
 
+// Members of the ensemble that one launch takes over nb windows (forward_prepare says why).
+static int launch_members(const gwd_model* m, int64_t batch_rows, int64_t nb, int64_t window) {
+    if (m->arch.kind != 1 || m->persistent) return 1;
+    const int64_t fit = std::min(batch_rows, kMostRows) / (nb * window);
+    return member_group(m, (int)std::max<int64_t>(1, std::min<int64_t>(m->n_members, fit)));
+}
+
+// Cost, in rows of one member, of a request of `rows` rows in total_win windows of `window`, nb_most of them a
+// batch. A set of launches over a batch costs as much as set_rows rows beside its own (one member, 256 |
+// 32,768 | 65,536 rows: BF16 0.25 | 0.51 | 0.74 ms, FP8 0.24 | 0.44 | 0.63, FP32 0.97 | 2.93 | 5.45), and
+// blocks of reserved rows that the windows do not fill are dispatched all the same: about set_rows / 8 per
+// row reserved for each row in use (8 windows of 262,144 with 4,096 rows each in use: 2.7 ms, not 0.5).
+static double request_cost(const gwd_model* m, int64_t rows, int64_t total_win, int64_t window, int64_t nb_most,
+                           int64_t batch_rows) {
+    const double set_rows = m->prec == GWD_FP32 ? 12288.0 : 32768.0;
+    const int64_t nb = std::min(nb_most, total_win), group = launch_members(m, batch_rows, nb, window);
+    const int64_t sets = (total_win + nb - 1) / nb * ((m->n_members + group - 1) / group);
+    const double reserved = (double)total_win * (double)window / (double)std::max<int64_t>(rows, 1);
+    return (double)rows * m->n_members + (double)sets * set_rows * (1.0 + reserved / 8.0);
+}
+
+// Of the longest windows allowed and their halves down to the request's own length, the cheapest; false
+// if the request's own windows cost less. (A window reserves the longest one's rows: with windows as long as
+// the longest stream, 64 s beside 4,000 streams of 1 s ran in 501 batches of 8 windows, four members in BF16
+// 5,504 ms; 524 ms so, 606 ms in the request's own windows.)
 static bool merged_windows(const gwd_model* m, const gwd_stream* streams, int n_streams, int64_t total_win, int& window,
                            int& stride) {
     const int64_t H = (rf_of(&m->arch) - 1 + 127) / 128 * 128;   // overlap: whole 128-row tiles
     int64_t longest = 0;
     for (int s = 0; s < n_streams; ++s) longest = std::max<int64_t>(longest, streams[s].length);
-    int64_t batch = std::min<int64_t>((int64_t)m->batch_windows * window, kMostRows);
+    const int64_t batch_rows = (int64_t)m->batch_windows * window;
+    int64_t batch = std::min<int64_t>(batch_rows, kMostRows);
     if (std::min(batch, longest) * kRowBytes > m->ws.bytes) batch = std::min(batch, allowed_bytes(m) / kRowBytes);
-    const int64_t cap = std::max<int64_t>(window, (n_streams == 1 ? batch : batch / 8) / 128 * 128);
-    int64_t W = (longest + 127) / 128 * 128, S = W;
-    if (W > cap) {
-        if (cap <= H) return false;
-        const int64_t n = (longest - H + cap - H - 1) / (cap - H);
-        S = ((longest - H + n - 1) / n + 127) / 128 * 128;
-        W = S + H;
+    const int own = window;
+    double best = request_cost(m, total_win * own, total_win, own, m->batch_windows, batch_rows);
+    bool merged = false;
+    int64_t cap = std::max<int64_t>(own, (n_streams == 1 ? batch : batch / 8) / 128 * 128);
+    for (;;) {
+        int64_t W = (longest + 127) / 128 * 128, S = W;
+        if (W > cap) {
+            if (cap <= H) break;
+            const int64_t n = (longest - H + cap - H - 1) / (cap - H);
+            S = ((longest - H + n - 1) / n + 127) / 128 * 128;
+            W = S + H;
+        }
+        int64_t rows = 0, wins = 0;
+        for (int s = 0; s < n_streams; ++s) {
+            const int64_t n = nwin_of(streams[s].length, (int)W, (int)S);
+            rows += streams[s].length + (n > 1 ? (n - 1) * (W - S) : 0);
+            wins += n;
+        }
+        const double cost = request_cost(m, rows, wins, W, std::max<int64_t>(1, batch_rows / W), batch_rows);
+        if (rows < total_win * own && cost < best) {
+            best = cost;
+            merged = true;
+            window = (int)W;
+            stride = (int)S;
+        }
+        if (cap <= own || W <= own) break;
+        cap = std::max<int64_t>(own, std::min(cap, W) / 2 / 128 * 128);
     }
-    int64_t rows = 0;
-    for (int s = 0; s < n_streams; ++s) {
-        const int64_t n = nwin_of(streams[s].length, (int)W, (int)S);
-        rows += streams[s].length + (n > 1 ? (n - 1) * (W - S) : 0);
-    }
-    if (rows >= total_win * window) return false;
-    window = (int)W;
-    stride = (int)S;
-    return true;
+    return merged;
 }
 
 gwd_status ensure_workspace(gwd_model* m, int64_t bytes, hipStream_t st) {
@@ -309,11 +347,7 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
     // the chip idle, or run each block for one chunk beside a warm-up chunk. Four members: BF16, 8 s
     // 1.98 -> 1.20 ms, five ragged FP8 streams of 22 s 5.94 -> 2.98 ms, two-branch, 32 s 3.25 -> 2.85 ms;
     // 256 s (two members per launch) 31.3 ms either way
-    fb.n_group = 1;
-    if (m->arch.kind == 1 && !persist) {
-        const int64_t fit = std::min(batch_rows, kMostRows) / ((int64_t)nb_max * window);
-        fb.n_group = member_group(m, (int)std::max<int64_t>(1, std::min<int64_t>(m->n_members, fit)));
-    }
+    fb.n_group = launch_members(m, batch_rows, nb_max, window);
     if (m->arch.kind == 1) {
         // long windows: cap the windows per batch (and the members per launch) so the activations stay
         // within the memory they may take

@@ -532,6 +532,27 @@ struct FusedMember {
     __device__ const T* weights(const T* q) const { return (const T*)((const char*)q + off); }
 };
 
+// A block's window, interleaved sub-sequence and segment of it. Merged windows end before their last segments
+// (win_rows), so they count segment by segment over all windows: with a window's segments side by side, blocks
+// with work and without alternate, and dealt round-robin to the XCDs they leave some of those idle (256
+// windows of 8,192 half in use, two of four segments: half the chip).
+struct FusedBlock {
+    int seg, cls, b;
+    template <class FA, class I>
+    __device__ FusedBlock(const FA& p, I bid) {
+        if (p.win_rows) {
+            const int per = p.mem_blocks / p.n_seg, i = bid % per;
+            seg = bid / per;
+            cls = i % p.d0;
+            b = i / p.d0;
+        } else {
+            seg = bid % p.n_seg;
+            cls = (bid / p.n_seg) % p.d0;
+            b = bid / (p.n_seg * p.d0);
+        }
+    }
+};
+
 __device__ inline uint8_t* fu_buf(uint8_t* lds, int j) { return lds + (j == 0 ? FU_B0 : j == 1 ? FU_B1 : FU_B2); }
 
 
