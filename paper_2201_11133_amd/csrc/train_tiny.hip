@@ -123,6 +123,23 @@ __global__ __launch_bounds__(TN) void tiny_fwd_kernel(const T* __restrict__ blob
     }
 }
 
+// dL/dwindows of one row, from dL/dpre of conv 0 at the row (dp) and at the next one (only where `tap`).
+template <class T>
+__device__ inline void tiny_du_row(const T* __restrict__ blob, const T (&dp)[TC], const T* next, bool tap, T* du) {
+    T s0 = 0, s1 = 0;
+#pragma unroll
+    for (int o = 0; o < TC; ++o) {
+        s0 += dp[o] * blob[4 * o + 1];
+        s1 += dp[o] * blob[4 * o + 3];
+        if (tap) {
+            s0 += next[o] * blob[4 * o + 0];
+            s1 += next[o] * blob[4 * o + 2];
+        }
+    }
+    du[0] = s0;
+    du[1] = s1;
+}
+
 // dL/dpre of every layer dp [4][M][16] and, if du, dL/dwindows. Block: one tile of TB_ROWS rows of one
 // window, thread tid the row t0 + tid, the layers in reverse with dL/dpre of its row in registers and, for
 // the taps of the rows to the left, in LDS. 64 windows of 4096: 295 us (three launches per layer) -> 37 us.
@@ -189,21 +206,19 @@ __global__ __launch_bounds__(TN) void tiny_bwd_kernel(const T* __restrict__ blob
     if (!du) return;
     store_row(D[0][tid], dp);
     __syncthreads();
-    if (own) {
-        T s0 = 0, s1 = 0;
-        const bool tap = t + 1 < Tw;
-#pragma unroll
-        for (int o = 0; o < TC; ++o) {
-            s0 += dp[o] * blob[4 * o + 1];
-            s1 += dp[o] * blob[4 * o + 3];
-            if (tap) {
-                s0 += D[0][tid + 1][o] * blob[4 * o + 0];
-                s1 += D[0][tid + 1][o] * blob[4 * o + 2];
-            }
-        }
-        du[2 * row] = s0;
-        du[2 * row + 1] = s1;
-    }
+    if (own) tiny_du_row(blob, dp, D[0][tid + 1], t + 1 < Tw, du + 2 * row);
+}
+
+// dL/dwindows alone, from dL/dpre of conv 0, for a du that shares memory with what the kernels above and below
+// read (an in-place gradient): it runs after them.
+template <class T>
+__global__ __launch_bounds__(TN) void tiny_du_kernel(const T* __restrict__ blob, const T* __restrict__ dpre, int64_t M,
+                                                     int Tw, T* __restrict__ du) {
+    const int64_t row = (int64_t)blockIdx.x * TN + threadIdx.x;
+    if (row >= M) return;
+    T dp[TC];
+    load_row(dpre + row * TC, dp);
+    tiny_du_row(blob, dp, dpre + (row + 1) * TC, row % Tw + 1 < Tw, du + 2 * row);
 }
 
 // Weight gradients, first level: part[j][p] = sum over the rows r = j (mod T_RES), in ascending order, of
@@ -406,10 +421,18 @@ hipError_t tiny_train_backward(const T* blob, const float* u, int B, int Tw, con
     const int64_t M = (int64_t)B * Tw;
     const int tiles = (Tw + TB_ROWS - 1) / TB_ROWS;
     T* part = scratch + 4 * M * TC;
+    const auto meets = [&](const void* p, int64_t bytes) {
+        const uintptr_t a = (uintptr_t)du, b = (uintptr_t)p;
+        return du && a < b + (uint64_t)bytes && b < a + (uint64_t)(2 * M * (int64_t)sizeof(T));
+    };
+    const bool last = meets(u, 2 * M * 4) || meets(dz, M * (int64_t)sizeof(T)) || meets(ys, 4 * M * TC * (int64_t)sizeof(T));
     hipLaunchKernelGGL(tiny_bwd_kernel<T>, dim3((unsigned)((int64_t)B * tiles)), dim3(TN), 0, st, blob, ys, dz, M, Tw,
-                       tiles, du, scratch);
+                       tiles, last ? nullptr : du, scratch);
     hipLaunchKernelGGL(tiny_wgrad_kernel<T>, dim3(T_RES), dim3(256), 0, st, u, ys, (const T*)scratch, dz, M, Tw, part);
     hipLaunchKernelGGL(tiny_reduce_kernel<T>, dim3((T_PARAMS + 15) / 16), dim3(256), 0, st, (const T*)part, grad);
+    if (last)
+        hipLaunchKernelGGL(tiny_du_kernel<T>, dim3((unsigned)((M + TN - 1) / TN)), dim3(TN), 0, st, blob, (const T*)scratch,
+                           M, Tw, du);
     return hipGetLastError();
 }
 
