@@ -398,7 +398,8 @@ gwd_status gwd_find_peaks(const double* x, int64_t n, double height, double min_
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return hip_fail(e, "hipGetDevice");
     // workspace: head and kept peaks [kmax] | edge bits and counts per tile | peaks [kmax] | widths [kmax] |
-    // block summaries | kept bits and counts per tile of peaks
+    // block summaries | kept bits and counts per tile of peaks: 16 bytes per sample, or 8 without room for the
+    // kept peaks where the device memory does not hold it (the host then takes them from all peaks and widths)
     const int64_t nt = (n + PK_TILE - 1) / PK_TILE;
     const int64_t kmax = n / 2 + 1, nkt = (kmax + PK_TILE - 1) / PK_TILE;
     const int64_t n1 = (n + PK_B1 - 1) / PK_B1, n2 = (n1 + PK_B1 - 1) / PK_B1;
@@ -408,26 +409,41 @@ gwd_status gwd_find_peaks(const double* x, int64_t n, double height, double min_
         need += (bytes + 15) / 16 * 16;
         return at;
     };
-    const int64_t off_out = take((int64_t)sizeof(PkHead) + std::max<int64_t>(kmax, PK_FIRST) * (int64_t)sizeof(PkOut));
+    const int64_t off_out = take((int64_t)sizeof(PkHead) + PK_FIRST * (int64_t)sizeof(PkOut));
     const int64_t off_mask = take(nt * PK_WORDS * 8), off_cnt = take((nt + 1) * 8);
     const int64_t off_cand = take(kmax * 8), off_w = take(kmax * 8);
     const int64_t off_s1 = take(n1 * (int64_t)sizeof(PkSum)), off_s2 = take(n2 * (int64_t)sizeof(PkSum));
     const int64_t off_km = take(nkt * PK_WORDS * 8), off_kc = take((nkt + 1) * 8);
+    const int64_t least = need, off_list = take((int64_t)sizeof(PkHead) + std::max<int64_t>(kmax, PK_FIRST) * (int64_t)sizeof(PkOut));
     std::lock_guard<std::mutex> lock(g_pk.mu);
     if (g_pk.bytes < need || g_pk.device != dev) {
-        if (g_pk.buf) {
-            (void)hipStreamSynchronize(st);
-            (void)hipFree(g_pk.buf);
-            g_pk.buf = nullptr;
-            g_pk.bytes = 0;
+        // grown only where there is room: a buffer that does without the list is not given up for a try in vain
+        size_t free_b = 0, total_b = 0;
+        const bool vain = g_pk.device == dev && g_pk.bytes >= least && hipMemGetInfo(&free_b, &total_b) == hipSuccess &&
+                          (int64_t)free_b + g_pk.bytes < need;
+        if (!vain) {
+            if (g_pk.buf) {
+                (void)hipStreamSynchronize(st);
+                (void)hipFree(g_pk.buf);
+                g_pk.buf = nullptr;
+                g_pk.bytes = 0;
+            }
+            g_pk.device = dev;
+            for (int64_t bytes : {need, least}) {
+                e = hipMalloc(&g_pk.buf, bytes);
+                if (e == hipSuccess) {
+                    g_pk.bytes = bytes;
+                    break;
+                }
+                g_pk.buf = nullptr;
+                (void)hipGetLastError();   // (the launches after a second try check it)
+            }
+            if (e != hipSuccess) return hip_fail(e, "hipMalloc(peak workspace)");
         }
-        e = hipMalloc(&g_pk.buf, need);
-        if (e != hipSuccess) return hip_fail(e, "hipMalloc(peak workspace)");
-        g_pk.bytes = need;
-        g_pk.device = dev;
     }
+    const bool list = g_pk.bytes >= need;
     char* b = (char*)g_pk.buf;
-    PkHead* head = (PkHead*)(b + off_out);
+    PkHead* head = (PkHead*)(b + (list ? off_list : off_out));
     PkOut* out = (PkOut*)(head + 1);
     uint64_t *mask = (uint64_t*)(b + off_mask), *kmask = (uint64_t*)(b + off_km);
     int64_t *counts = (int64_t*)(b + off_cnt), *kcount = (int64_t*)(b + off_kc), *cand = (int64_t*)(b + off_cand);
@@ -442,8 +458,9 @@ gwd_status gwd_find_peaks(const double* x, int64_t n, double height, double min_
     hipLaunchKernelGGL(pk_width_kernel, dim3(wblocks), dim3(256), 0, st, x, n, cand, counts + nt, s1, s2, min_width, wd,
                        kmask, kcount);
     hipLaunchKernelGGL(pk_kept_scan_kernel, dim3(1), dim3(256), 0, st, counts + nt, kcount, head);
-    hipLaunchKernelGGL(pk_kept_kernel, dim3((unsigned)std::min<int64_t>(nkt, 1024)), dim3(256), 0, st, counts + nt, kmask,
-                       kcount, cand, wd, out);
+    if (list)
+        hipLaunchKernelGGL(pk_kept_kernel, dim3((unsigned)std::min<int64_t>(nkt, 1024)), dim3(256), 0, st, counts + nt, kmask,
+                           kcount, cand, wd, out);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "peak kernel launch");
     // the count and the first peaks in one copy, any others in a second one
@@ -457,19 +474,34 @@ gwd_status gwd_find_peaks(const double* x, int64_t n, double height, double min_
     if (first.head.bad) { set_error("gwd_find_peaks: NaN or Inf in the signal"); return GWD_ERR_NONFINITE; }
     const int64_t found = first.head.found, ncopy = std::min(found, capacity);
     std::vector<PkOut> rest;
-    if (ncopy > PK_FIRST) {
-        try {
+    std::vector<int64_t> all_p;
+    std::vector<double> all_w;
+    try {
+        if (!list && ncopy > 0) {
+            int64_t k = 0;
+            e = hipMemcpyAsync(&k, counts + nt, sizeof k, hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e != hipSuccess) return hip_fail(e, "peak count copy");
+            all_p.resize((size_t)k);
+            all_w.resize((size_t)k);
+            e = hipMemcpyAsync(all_p.data(), cand, k * sizeof(int64_t), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipMemcpyAsync(all_w.data(), wd, k * sizeof(double), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e != hipSuccess) return hip_fail(e, "peak copy");
+        } else if (ncopy > PK_FIRST) {
             rest.resize((size_t)(ncopy - PK_FIRST));
-        } catch (const std::bad_alloc&) {
-            set_error("gwd_find_peaks: out of host memory");
-            return GWD_ERR_ARG;
+            e = hipMemcpyAsync(rest.data(), out + PK_FIRST, rest.size() * sizeof(PkOut), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess) e = hipStreamSynchronize(st);
+            if (e != hipSuccess) return hip_fail(e, "peak copy");
         }
-        e = hipMemcpyAsync(rest.data(), out + PK_FIRST, rest.size() * sizeof(PkOut), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return hip_fail(e, "peak copy");
+    } catch (const std::bad_alloc&) {
+        set_error("gwd_find_peaks: out of host memory");
+        return GWD_ERR_ARG;
     }
-    for (int64_t c = 0; c < ncopy; ++c) {
-        const PkOut& o = c < PK_FIRST ? first.out[c] : rest[(size_t)(c - PK_FIRST)];
+    for (int64_t c = 0, i = 0; c < ncopy; ++c, ++i) {
+        if (!list)
+            while (!(all_w[(size_t)i] >= min_width)) ++i;   // (the device counted ncopy of them)
+        const PkOut o = !list ? PkOut{all_p[(size_t)i], all_w[(size_t)i]} : c < PK_FIRST ? first.out[c] : rest[(size_t)(c - PK_FIRST)];
         peaks[c] = o.peak;
         widths[c] = o.width;
     }

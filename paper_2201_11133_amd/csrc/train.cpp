@@ -31,9 +31,23 @@ static gwd_status ensure_tws(gwd_model* m, int64_t bytes, hipStream_t st) {
         m->tws.bytes = 0;
     }
     e = hipMalloc(&m->tws.base, bytes);
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(training workspace)");
+    if (e != hipSuccess) {
+        m->tws.base = nullptr;
+        (void)hipGetLastError();   // (the launches after a second try check it)
+        return hip_fail(e, "hipMalloc(training workspace)");
+    }
     m->tws.bytes = bytes;
     return GWD_OK;
+}
+
+// `bytes` where the device memory holds them, else `least`: m->tws.bytes says which.
+static gwd_status ensure_tws(gwd_model* m, int64_t bytes, int64_t least, hipStream_t st) {
+    if (m->tws.bytes < bytes && m->tws.bytes >= least) {   // (grown only where there is room, not tried in vain each call)
+        size_t free_b = 0, total_b = 0;
+        if (hipMemGetInfo(&free_b, &total_b) == hipSuccess && (int64_t)free_b + m->tws.bytes < bytes) return GWD_OK;
+    }
+    const gwd_status s = ensure_tws(m, bytes, st);
+    return s == GWD_OK || least >= bytes ? s : ensure_tws(m, least, st);
 }
 
 static gwd_status check_train(const gwd_model* m, int member, const void* windows, int B, int T, const char* who) {
@@ -140,20 +154,20 @@ static gwd_status bwd_kind1(gwd_model* m, int member, const float* u, int B, int
     const int mid = m->arch.head_mid_relu;
     BlobOffsets v = blob_offsets(m->arch);
     const float* w = (const float*)m->canon[member];
-    // weight-gradient partials: one chunk per window, or split windows (gemm_wgrad: at most 1,023 output
-    // tiles of 128 x 128 or 383 of 256 x 256 then)
-    const int64_t nch = std::max<int64_t>(B, 384);
     // workspace (floats): XS[LPS][M][128] PRE[LPS][M][256] G DG DX DSKIP SKS R H DH AH [M][128] each, partials
     const int64_t f_xs = 0, f_pre = f_xs + (int64_t)LPS * M * kC, f_g = f_pre + (int64_t)LPS * M * 2 * kC;
     const int64_t f_dg = f_g + M * kC, f_dx = f_dg + M * kC, f_ds = f_dx + M * kC, f_sks = f_ds + M * kC;
     const int64_t f_r = f_sks + M * kC, f_h = f_r + M * kC, f_dh = f_h + M * kC, f_ah = f_dh + M * kC;
     const int64_t f_dpre = f_ah + M * kC, f_bt = f_dpre + M * 2 * kC, f_part = f_bt + 2 * kC * 2 * kC;
-    // partials of the largest weight-gradient product (2C x 2C per chunk), then the group sums of
-    // its two-stage reduction (at most 64 groups)
-    const int64_t f_cpart = f_part + (nch + 64) * 2 * kC * 2 * kC;   // column sums fused into them
-    const int64_t total = f_cpart + (4 * nch + 64) * 2 * kC;
-    gwd_status s = ensure_tws(m, total * 4, st);
+    // partials of the weight-gradient products: one chunk per window (2C x 2C), the group sums of their two-stage
+    // reduction (at most 64 groups) and the column sums fused into them; with split windows (gemm_wgrad) more
+    // of them, for small batches, where the device memory holds it (8 windows of 4,096: 38 MB, not 19)
+    const int64_t least = ((int64_t)B + 64) * 2 * kC * 2 * kC, least_c = ((int64_t)B + 64) * 2 * kC;
+    const int64_t most = std::max(least, wgrad_part_floats(M, T)), most_c = std::max<int64_t>(least_c, 1088 * 2 * kC);
+    gwd_status s = ensure_tws(m, (f_part + most + most_c) * 4, (f_part + least + least_c) * 4, st);
     if (s != GWD_OK) return s;
+    const bool roomy = m->tws.bytes >= (f_part + most + most_c) * 4;
+    const int64_t f_cpart = f_part + (roomy ? most : least), total = f_cpart + (roomy ? most_c : least_c);
     void* b = m->tws.base;
     float *G = fptr(b, f_g), *DG = fptr(b, f_dg), *DX = fptr(b, f_dx), *DS = fptr(b, f_ds), *SKS = fptr(b, f_sks);
     float *R = fptr(b, f_r), *H = fptr(b, f_h), *DH = fptr(b, f_dh), *AH = fptr(b, f_ah), *DPRE = fptr(b, f_dpre);
@@ -380,14 +394,17 @@ gwd_status gwd_backward(gwd_model* m, int32_t member, const float* windows, int3
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     if (m->arch.kind == 0) {
         const size_t es = m->prec == GWD_FP64 ? 8 : 4;
-        s = ensure_tws(m, tiny_train_backward_scratch(B, W) * (int64_t)es, st);
+        const int few = tiny_train_windows(B, W);
+        const int64_t all = tiny_train_backward_scratch(B, W) * (int64_t)es;
+        s = ensure_tws(m, all, tiny_train_backward_scratch(few, W) * (int64_t)es, st);
         if (s != GWD_OK) return s;
+        const int windows_at_once = m->tws.bytes >= all ? B : few;
         if (m->prec == GWD_FP64)
-            e = tiny_train_backward<double>((const double*)m->canon[member], windows, B, W, (const double*)saved,
+            e = tiny_train_backward<double>((const double*)m->canon[member], windows, B, windows_at_once, W, (const double*)saved,
                                             (const double*)grad_logit, (double*)grad_params, (double*)m->tws.base,
                                             (double*)grad_input, st);
         else
-            e = tiny_train_backward<float>((const float*)m->canon[member], windows, B, W, (const float*)saved,
+            e = tiny_train_backward<float>((const float*)m->canon[member], windows, B, windows_at_once, W, (const float*)saved,
                                            (const float*)grad_logit, (float*)grad_params, (float*)m->tws.base,
                                            (float*)grad_input, st);
         return e == hipSuccess ? GWD_OK : hip_fail(e, "small member backward");

@@ -88,6 +88,9 @@ struct WgradDst {
 };
 
 hipError_t gemm_rows(const GemmRowsArgs& a, hipStream_t st);
+// Floats at WgradArgs::part with which the products of a backward over M rows in windows of T split their
+// windows as they like (up to 256 x 256 outputs; with less, gemm_wgrad splits them less).
+int64_t wgrad_part_floats(int64_t M, int T);
 // With a.cpart set, cdst receives the column sums of A (element k of the Ktot sums, mapped like dst).
 hipError_t gemm_wgrad(const WgradArgs& a, const WgradDst& dst, hipStream_t st, const WgradDst* cdst = nullptr);
 // dst[n * dst_stride] += sum_rows f(X[row][n]) * w[row * wstride]   (w optional, f = id or ReLU; N = 4 c and
@@ -131,9 +134,11 @@ hipError_t launch_bce(const float* z, const float* y, int64_t n, float* grad, do
 template <class T>
 hipError_t tiny_train_forward(const T* blob, const float* u, int B, int Tw, T* ys /*[4][M][16]*/, T* logits,
                               hipStream_t st);
-int64_t tiny_train_backward_scratch(int B, int Tw);   // values of T the backward needs as scratch
+// values of T the backward needs as scratch, `windows` windows at a time: B, or tiny_train_windows
+int64_t tiny_train_backward_scratch(int windows, int Tw);
+int tiny_train_windows(int B, int Tw);
 template <class T>
-hipError_t tiny_train_backward(const T* blob, const float* u, int B, int Tw, const T* ys, const T* dz, T* grad,
+hipError_t tiny_train_backward(const T* blob, const float* u, int B, int windows, int Tw, const T* ys, const T* dz, T* grad,
                                T* scratch, T* du, hipStream_t st);
 
 }  // namespace gwd

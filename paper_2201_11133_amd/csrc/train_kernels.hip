@@ -5,6 +5,8 @@
 // Row index `row` = b * T + t addresses time step t of window b; an operand part with shift s reads
 // row b * T + (t + s) and is zero when t + s falls outside [0, T) (each window has zero context, so
 // a dilation tap never crosses windows).
+#include <algorithm>
+
 #include "gwd_internal.h"
 #include "train_internal.h"
 
@@ -1042,10 +1044,31 @@ hipError_t gemm_rows(const GemmRowsArgs& a, hipStream_t st) {
 // Rows per chunk: whole windows when they give a block for each of the chip's 512 slots (two per CU), else
 // windows halved, down to 128 rows (two steps of the bf16 kernel). 8 windows of 4,096 rows have 8 chunks
 // otherwise, 32 blocks or fewer; 128 windows the same 512 blocks for the conv taps, but 256 for skip and residual.
-static int64_t wgrad_rows(const WgradArgs& a, int64_t tiles, int64_t blocks) {
-    int64_t rpc = a.T;
-    while ((a.M / rpc) * tiles < blocks && rpc % 256 == 0) rpc /= 2;
+static int64_t wgrad_rows(int64_t M, int T, int64_t tiles, int64_t blocks) {
+    int64_t rpc = T;
+    while ((M / rpc) * tiles < blocks && rpc % 256 == 0) rpc /= 2;
     return rpc;
+}
+
+// Partial sums of `chunks` chunks, and the group sums that reduce_parts puts behind 128 or more.
+static int64_t wgrad_floats(int64_t chunks, int64_t KN) { return (chunks + (chunks >= 128 ? 16 : 0)) * KN; }
+
+// Rows per chunk of the 256 x 256 tile, 0 where it does not pay: enough chunks for three quarters of the CUs,
+// long enough (16 steps) to be worth their partial sums of 256 KB each (128 windows of 4,096: 33 MB more, 4 us
+// of reduction for the 41 us gained).
+static int64_t wgrad_rows_t256(int64_t M, int T) {
+    const int64_t rpc = wgrad_rows(M, T, 1, 192);
+    return rpc >= 1024 && M / rpc >= 192 ? rpc : 0;
+}
+
+int64_t wgrad_part_floats(int64_t M, int T) {
+    int64_t most = 0;
+    for (int tiles : {1, 2, 4}) {   // 128 x 128, 256 x 128, 256 x 256
+        int64_t rpc = wgrad_rows(M, T, tiles, 512);
+        if (tiles == 4 && wgrad_rows_t256(M, T)) rpc = std::min(rpc, wgrad_rows_t256(M, T));
+        most = std::max(most, wgrad_floats(M / rpc, (int64_t)tiles * W2T * W2T));
+    }
+    return most;
 }
 
 hipError_t gemm_wgrad(const WgradArgs& a0, const WgradDst& d, hipStream_t st, const WgradDst* cdst) {
@@ -1060,16 +1083,16 @@ hipError_t gemm_wgrad(const WgradArgs& a0, const WgradDst& d, hipStream_t st, co
         ok = ok && q.K % W2T == 0 && q.ld % 8 == 0 && ((uintptr_t)(q.p16 ? (const void*)q.p16 : q.ptr) & 15) == 0;
     }
     if (!ok || (a.cpart && (!cdst || a.A[0].shift != 0 || (a.nparts > 1 && a.A[1].shift != 0)))) return hipErrorInvalidValue;
-    a.rows_per_chunk = wgrad_rows(a, (a.Ktot / W2T) * (a.N / W2T), 512);
-    // the 256 x 256 tile: enough chunks for three quarters of the CUs, long enough (16 steps) to be worth their
-    // partial sums of 256 KB each (128 windows of 4,096: 33 MB more, 4 us of reduction for the 41 us gained)
-    bool t256 = a.bf16 && a.nparts == 1 && a.Ktot == W3T && a.N == W3T && a.nbparts == 2 && a.A[0].p16 && a.B16 &&
-                a.A[0].shift == 0;
-    if (t256) {
-        const int64_t rpc = wgrad_rows(a, 1, 192);
-        t256 = rpc >= 1024 && a.M / rpc >= 192;
-        if (t256) a.rows_per_chunk = rpc;
-    }
+    a.rows_per_chunk = wgrad_rows(a.M, a.T, (a.Ktot / W2T) * (a.N / W2T), 512);
+    const int64_t r256 = wgrad_rows_t256(a.M, a.T);
+    const bool t256 = r256 && a.bf16 && a.nparts == 1 && a.Ktot == W3T && a.N == W3T && a.nbparts == 2 && a.A[0].p16 &&
+                      a.B16 && a.A[0].shift == 0;
+    if (t256) a.rows_per_chunk = r256;
+    // (where the workspace holds less than it might, fewer and longer chunks)
+    const auto fits = [&](int64_t n) {
+        return wgrad_floats(n, (int64_t)a.Ktot * a.N) <= a.part_capacity && (!a.cpart || wgrad_floats(n, a.Ktot) <= a.cpart_capacity);
+    };
+    while (a.rows_per_chunk < a.T && !fits(a.M / a.rows_per_chunk)) a.rows_per_chunk *= 2;
     const int nchunks = (int)(a.M / a.rows_per_chunk);
     if ((int64_t)nchunks * a.Ktot * a.N > a.part_capacity || (a.cpart && (int64_t)nchunks * a.Ktot > a.cpart_capacity))
         return hipErrorInvalidValue;

@@ -142,10 +142,11 @@ __device__ inline void tiny_du_row(const T* __restrict__ blob, const T (&dp)[TC]
 
 // dL/dpre of every layer dp [4][M][16] and, if du, dL/dwindows. Block: one tile of TB_ROWS rows of one
 // window, thread tid the row t0 + tid, the layers in reverse with dL/dpre of its row in registers and, for
-// the taps of the rows to the left, in LDS. 64 windows of 4096: 295 us (three launches per layer) -> 37 us.
+// the taps of the rows to the left, in LDS. ym: rows from one layer of ys to the next (M is that of dp).
+// 64 windows of 4096: 295 us (three launches per layer) -> 37 us.
 template <class T>
 __global__ __launch_bounds__(TN) void tiny_bwd_kernel(const T* __restrict__ blob, const T* __restrict__ ys,
-                                                      const T* __restrict__ dz, int64_t M, int Tw, int tiles,
+                                                      const T* __restrict__ dz, int64_t M, int64_t ym, int Tw, int tiles,
                                                       T* __restrict__ du, T* __restrict__ dpre) {
     constexpr int LD = tiny_ld<T>();
     __shared__ __attribute__((aligned(16))) T D[2][TN][LD];
@@ -159,7 +160,7 @@ __global__ __launch_bounds__(TN) void tiny_bwd_kernel(const T* __restrict__ blob
     T y[TC], dp[TC];
     {
         const T g = dz[lrow];
-        load_row(ys + ((int64_t)3 * M + lrow) * TC, y);
+        load_row(ys + ((int64_t)3 * ym + lrow) * TC, y);
         const T* wo = blob + tiny_off(4);
 #pragma unroll
         for (int c = 0; c < TC; ++c) {
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(TN) void tiny_bwd_kernel(const T* __restrict__ blob
         const int d = 1 << layer;
         store_row(D[layer & 1][tid], dp);
         if (own) store_row(dpre + ((int64_t)layer * M + row) * TC, dp);
-        load_row(ys + ((int64_t)(layer - 1) * M + lrow) * TC, y);
+        load_row(ys + ((int64_t)(layer - 1) * ym + lrow) * TC, y);
         __syncthreads();
         // dL/dy of the layer below, then through its ReLU
         const T* W = blob + tiny_off(layer);
@@ -226,7 +227,8 @@ __global__ __launch_bounds__(TN) void tiny_du_kernel(const T* __restrict__ blob,
 // consecutive residues j, one per wave): groups 0-2 the conv layers 1-3, lane (o pair, c pair) of both taps,
 // group 3 conv 0 and the output layer. T_STEP steps (64 rows) of each operand go through LDS as one 16-byte
 // load per thread, T_DEEP stages ahead: with every lane loading its own operands the vector-memory
-// instructions bounded it. 64 windows of 4096: 2,660 us (one block per parameter walking every row),
+// instructions bounded it. more: the rows go on from those of the call before (whole windows, a multiple of
+// T_RES rows so far), whose sums are in part. 64 windows of 4096: 2,660 us (one block per parameter walking every row),
 // 337 us with a block per residue reading its operands directly, 105 us now; the 200 MB it reads
 // take 40 us at the rate of a large copy.
 constexpr int T_STEP = 16, T_DEEP = 3;
@@ -254,7 +256,7 @@ struct TinyStage {
 template <class T>
 __global__ __launch_bounds__(256) void tiny_wgrad_kernel(const float* __restrict__ u, const T* __restrict__ ys,
                                                          const T* __restrict__ dpre, const T* __restrict__ dz, int64_t M,
-                                                         int Tw, T* __restrict__ part) {
+                                                         int64_t ym, int Tw, int more, T* __restrict__ part) {
     constexpr int SZ = T_STEP * 4 * TC;
     __shared__ __attribute__((aligned(16))) T sd[2][SZ], sx[2][SZ], so[2][SZ];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(256) void tiny_wgrad_kernel(const float* __restrict
     if (group < 3) {
         const int layer = group + 1, d = 1 << layer, o = 2 * (lane >> 3), c = 2 * (lane & 7);
         const T* D = dpre + (int64_t)layer * M * TC;
-        const T* X = ys + (int64_t)(layer - 1) * M * TC;
+        const T* X = ys + (int64_t)(layer - 1) * ym * TC;
         TinyStage<T> pd[T_DEEP], px[T_DEEP], po[T_DEEP];
         auto load = [&](int k, int st) __attribute__((always_inline)) {
             pd[k].load(D, st, j0, 0, M, tid);
@@ -275,6 +277,16 @@ __global__ __launch_bounds__(256) void tiny_wgrad_kernel(const float* __restrict
             po[k].load(X, st, j0, d, M, tid);
         };
         T a[2][2][2] = {}, ab[2] = {};             // [o][c][tap], biases
+        T* w = out + tiny_off(layer);
+        if (more)
+#pragma unroll
+            for (int oi = 0; oi < 2; ++oi) {
+#pragma unroll
+                for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+                    for (int tap = 0; tap < 2; ++tap) a[oi][ci][tap] = w[((o + oi) * TC + c + ci) * 2 + tap];
+                ab[oi] = w[TC * TC * 2 + o + oi];
+            }
 #pragma unroll
         for (int k = 0; k < T_DEEP; ++k) load(k, k);
         for (int st0 = 0; st0 < nst; st0 += T_DEEP)
@@ -316,7 +328,6 @@ __global__ __launch_bounds__(256) void tiny_wgrad_kernel(const float* __restrict
                     for (int i = 0; i < rows; ++i) add(i);
                 }
             }
-        T* w = out + tiny_off(layer);
 #pragma unroll
         for (int oi = 0; oi < 2; ++oi) {
 #pragma unroll
@@ -333,7 +344,7 @@ __global__ __launch_bounds__(256) void tiny_wgrad_kernel(const float* __restrict
     T pz[T_DEEP][5];
     auto load = [&](int k, int st) __attribute__((always_inline)) {
         pd[k].load(dpre, st, j0, 0, M, tid);
-        py[k].load(ys + 3 * M * TC, st, j0, 0, M, tid);
+        py[k].load(ys + 3 * ym * TC, st, j0, 0, M, tid);
         const int64_t r = min((int64_t)T_RES * (st * T_STEP + (lane >> 2)) + j0 + (lane & 3), M - 1);
         const int64_t rp = max(r - 1, (int64_t)0);
         pz[k][0] = dz[r];
@@ -344,6 +355,11 @@ __global__ __launch_bounds__(256) void tiny_wgrad_kernel(const float* __restrict
     };
     const int o = lane >> 2, c = (lane >> 1) & 1, tap = lane & 1;
     T a0 = 0, a1 = 0;
+    T* w1 = lane < 16 ? out + 64 + lane : out + tiny_off(4) + min(lane, 32) - 16;
+    if (more) {
+        a0 = out[lane];
+        a1 = *w1;
+    }
 #pragma unroll
     for (int k = 0; k < T_DEEP; ++k) load(k, k);
     for (int st0 = 0; st0 < nst; st0 += T_DEEP)
@@ -380,8 +396,7 @@ __global__ __launch_bounds__(256) void tiny_wgrad_kernel(const float* __restrict
             }
         }
     out[lane] = a0;
-    if (lane < 16) out[64 + lane] = a1;
-    else if (lane < 33) out[tiny_off(4) + lane - 16] = a1;
+    if (lane < 33) *w1 = a1;
 }
 
 // grad[p] = the residues' sums added pairwise (j + 128, + 64, .. + 1).
@@ -405,7 +420,17 @@ __global__ __launch_bounds__(256) void tiny_reduce_kernel(const T* __restrict__ 
     if (run == 0 && i < T_PARAMS) grad[i] = red[0][p];
 }
 
-int64_t tiny_train_backward_scratch(int B, int Tw) { return 4 * (int64_t)B * Tw * TC + T_RES * T_PARAMS; }
+// dL/dpre of `windows` windows at a time, then the partial sums.
+int64_t tiny_train_backward_scratch(int windows, int Tw) { return 4 * (int64_t)windows * Tw * TC + T_RES * T_PARAMS; }
+
+// Windows at a time where device memory does not hold the scratch of all B: about a quarter, and a multiple of
+// T_RES rows, so that the sums keep their order (B: no such number).
+int tiny_train_windows(int B, int Tw) {
+    int unit = T_RES;   // windows of a multiple of T_RES rows
+    while (unit > 1 && (int64_t)(unit / 2) * Tw % T_RES == 0) unit /= 2;
+    const int w = (B / 4 + unit - 1) / unit * unit;
+    return w < 1 || w > B ? B : w;
+}
 
 template <class T>
 hipError_t tiny_train_forward(const T* blob, const float* u, int B, int Tw, T* ys, T* logits, hipStream_t st) {
@@ -416,19 +441,25 @@ hipError_t tiny_train_forward(const T* blob, const float* u, int B, int Tw, T* y
 }
 
 template <class T>
-hipError_t tiny_train_backward(const T* blob, const float* u, int B, int Tw, const T* ys, const T* dz, T* grad,
+hipError_t tiny_train_backward(const T* blob, const float* u, int B, int windows, int Tw, const T* ys, const T* dz, T* grad,
                                T* scratch, T* du, hipStream_t st) {
     const int64_t M = (int64_t)B * Tw;
     const int tiles = (Tw + TB_ROWS - 1) / TB_ROWS;
-    T* part = scratch + 4 * M * TC;
+    T* part = scratch + 4 * (int64_t)windows * Tw * TC;
     const auto meets = [&](const void* p, int64_t bytes) {
         const uintptr_t a = (uintptr_t)du, b = (uintptr_t)p;
         return du && a < b + (uint64_t)bytes && b < a + (uint64_t)(2 * M * (int64_t)sizeof(T));
     };
     const bool last = meets(u, 2 * M * 4) || meets(dz, M * (int64_t)sizeof(T)) || meets(ys, 4 * M * TC * (int64_t)sizeof(T));
-    hipLaunchKernelGGL(tiny_bwd_kernel<T>, dim3((unsigned)((int64_t)B * tiles)), dim3(TN), 0, st, blob, ys, dz, M, Tw,
-                       tiles, last ? nullptr : du, scratch);
-    hipLaunchKernelGGL(tiny_wgrad_kernel<T>, dim3(T_RES), dim3(256), 0, st, u, ys, (const T*)scratch, dz, M, Tw, part);
+    if (last && windows < B) return hipErrorOutOfMemory;   // (it needs every window's dL/dpre at the end)
+    for (int b0 = 0; b0 < B; b0 += windows) {
+        const int nb = B - b0 < windows ? B - b0 : windows;
+        const int64_t r0 = (int64_t)b0 * Tw, m = (int64_t)nb * Tw;
+        hipLaunchKernelGGL(tiny_bwd_kernel<T>, dim3((unsigned)((int64_t)nb * tiles)), dim3(TN), 0, st, blob, ys + r0 * TC,
+                           dz + r0, m, M, Tw, tiles, last || !du ? nullptr : du + 2 * r0, scratch);
+        hipLaunchKernelGGL(tiny_wgrad_kernel<T>, dim3(T_RES), dim3(256), 0, st, u + 2 * r0, ys + r0 * TC, (const T*)scratch,
+                           dz + r0, m, M, Tw, b0 > 0 ? 1 : 0, part);
+    }
     hipLaunchKernelGGL(tiny_reduce_kernel<T>, dim3((T_PARAMS + 15) / 16), dim3(256), 0, st, (const T*)part, grad);
     if (last)
         hipLaunchKernelGGL(tiny_du_kernel<T>, dim3((unsigned)((M + TN - 1) / TN)), dim3(TN), 0, st, blob, (const T*)scratch,
@@ -438,9 +469,9 @@ hipError_t tiny_train_backward(const T* blob, const float* u, int B, int Tw, con
 
 template hipError_t tiny_train_forward<float>(const float*, const float*, int, int, float*, float*, hipStream_t);
 template hipError_t tiny_train_forward<double>(const double*, const float*, int, int, double*, double*, hipStream_t);
-template hipError_t tiny_train_backward<float>(const float*, const float*, int, int, const float*, const float*,
+template hipError_t tiny_train_backward<float>(const float*, const float*, int, int, int, const float*, const float*,
                                                float*, float*, float*, hipStream_t);
-template hipError_t tiny_train_backward<double>(const double*, const float*, int, int, const double*, const double*,
+template hipError_t tiny_train_backward<double>(const double*, const float*, int, int, int, const double*, const double*,
                                                 double*, double*, double*, hipStream_t);
 
 }  // namespace gwd
