@@ -566,11 +566,15 @@ gwd_status gwd_debug_capture_backward(gwd_model* model, int32_t layer, float* x_
 /* Measurement support: issues the launch that gwd_forward makes at middle gated
  * layer `layer` of member `member` (the single-layer kernel, or the fused
  * kernel when a fused launch starts there; every layer it covers must be a
- * middle one) reps + 1 times, with the forward's grid over its batch
- * of windows, on the activations the last gwd_forward left in the model's
- * workspace, and times the last `reps` launches between two HIP events
- * recorded on hip_stream. Writes the average milliseconds per launch, the
- * windows per launch and the layers per launch (1, 3, 4 or 6). Requires a prior
+ * middle one) reps + 1 times, with the forward's grid over its first batch
+ * of windows and the members it takes together, on the activations the last
+ * gwd_forward left in the model's workspace, and times the last `reps`
+ * launches between two HIP events recorded on hip_stream. Writes the average
+ * milliseconds per launch, the windows per launch (those of the batch times
+ * the members of the launch; merged windows, gwd_set_window_merging, are
+ * longer than the request's and end at their streams' ends: switch merging
+ * off to time windows of a known length) and the layers per launch (1, 3, 4
+ * or 6). Requires a prior
  * gwd_forward on the model; synchronises hip_stream. The workspace contents
  * are overwritten. */
 gwd_status gwd_debug_time_layer(gwd_model* model, int32_t member, int32_t layer, int32_t reps,

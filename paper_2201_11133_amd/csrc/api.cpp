@@ -410,8 +410,12 @@ gwd_status forward_prepare(gwd_model* m, const gwd_stream* streams, int32_t n_st
         e = hipMemcpyAsync(d_tab, host_tab.data(), host_tab.size(), hipMemcpyHostToDevice, st);
     }
     if (e != hipSuccess) return hip_fail(e, "stream table upload");
-    m->last_nb = persist ? 0 : nb_max;   // (the persistent buffers are not the batch layout)
-    m->last_T = window;
+    m->last.nb = persist ? 0 : nb_max;   // (the persistent buffers are not the batch layout)
+    m->last.T = window;
+    m->last.n_group = fb.n_group;
+    m->last.act_stride = fb.act_stride;
+    m->last.rows = merged ? (const int32_t*)((const char*)d_tab + desc_bytes + first_bytes) : nullptr;
+    m->last.h_rows.assign(rows.begin(), rows.begin() + std::min<size_t>(rows.size(), (size_t)nb_max));
     fb.streams = d_tab;
     fb.firsts = (const int64_t*)((const char*)d_tab + desc_bytes);
     fb.rows = merged ? (const int32_t*)((const char*)d_tab + desc_bytes + first_bytes) : nullptr;
@@ -761,12 +765,21 @@ gwd_status gwd_debug_time_layer(gwd_model* m, int32_t member, int32_t layer, int
     const int L = m->arch.n_stacks * m->arch.layers_per_stack;
     if (member < 0 || member >= m->n_members || layer < 1 || layer + layers_per_launch(m, layer) > L - 1) { set_error("gwd_debug_time_layer: member or layer out of range (middle layers only)"); return GWD_ERR_ARG; }
     if (reps < 1 || reps > 1000) { set_error("gwd_debug_time_layer: reps not in [1, 1000]"); return GWD_ERR_ARG; }
-    if (m->last_nb == 0 || !m->ws.base) { set_error("gwd_debug_time_layer: run gwd_forward on this model first"); return GWD_ERR_ARG; }
+    const gwd_model::LastBatch& last = m->last;
+    if (last.nb == 0 || !m->ws.base) { set_error("gwd_debug_time_layer: run gwd_forward on this model first"); return GWD_ERR_ARG; }
     hipStream_t st = (hipStream_t)hip_stream;
     hipError_t e = hipSetDevice(m->device);
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     const int64_t tab_bytes = m->ws_tab_bytes;
-    const int64_t act = (int64_t)m->last_nb * m->last_T * kC * 4;
+    const int64_t act = last.n_group * last.act_stride * 4;
+    FwdBatch fb{};   // the launch that holds the member, over the first batch
+    fb.nb = last.nb;
+    fb.T = last.T;
+    fb.member = member - member % last.n_group;
+    fb.n_group = std::min<int>(last.n_group, m->n_members - fb.member);
+    fb.act_stride = last.act_stride;
+    fb.rows = last.rows;
+    fb.h_rows = last.rows ? last.h_rows.data() : nullptr;
     char* base = (char*)m->ws.base;
     void* x_a = base + tab_bytes;
     void* x_b = base + tab_bytes + act;
@@ -774,11 +787,10 @@ gwd_status gwd_debug_time_layer(gwd_model* m, int32_t member, int32_t layer, int
     hipEvent_t e0, e1;
     if ((e = hipEventCreate(&e0)) != hipSuccess) return hip_fail(e, "hipEventCreate");
     if ((e = hipEventCreate(&e1)) != hipSuccess) { (void)hipEventDestroy(e0); return hip_fail(e, "hipEventCreate"); }
-    e = launch_layer_production(m, member, layer, x_a, x_b, skip, m->last_nb, m->last_T, st);   // warm-up
+    e = launch_layer_production(m, layer, x_a, x_b, skip, fb, st);   // warm-up
     if (e == hipSuccess) e = hipEventRecord(e0, st);
     for (int i = 0; i < reps && e == hipSuccess; ++i)
-        e = launch_layer_production(m, member, layer, (i & 1) ? x_b : x_a, (i & 1) ? x_a : x_b, skip, m->last_nb,
-                                    m->last_T, st);
+        e = launch_layer_production(m, layer, (i & 1) ? x_b : x_a, (i & 1) ? x_a : x_b, skip, fb, st);
     if (e == hipSuccess) e = hipEventRecord(e1, st);
     if (e == hipSuccess) e = hipEventSynchronize(e1);
     float ms = 0.f;
@@ -787,7 +799,7 @@ gwd_status gwd_debug_time_layer(gwd_model* m, int32_t member, int32_t layer, int
     (void)hipEventDestroy(e1);
     if (e != hipSuccess) return hip_fail(e, "layer timing");
     *ms_per_launch = ms / reps;
-    *windows_per_launch = m->last_nb;
+    *windows_per_launch = fb.nb * fb.n_group;
     *layers_per_launch_out = layers_per_launch(m, layer);
     return GWD_OK;
 }

@@ -1130,30 +1130,29 @@ hipError_t launch_bf16_to_f32(const uint16_t* x, int64_t n, float* y, hipStream_
 
 // One launch of layer l exactly as the forward issues it for a middle layer (workspace buffers).
 template <bool FP8>
-static hipError_t production_lp(gwd_model* m, int member, int l, void* x_in, void* x_out, float* skip, int nb, int T,
+static hipError_t production_lp(gwd_model* m, int l, void* x_in, void* x_out, float* skip, const FwdBatch& fb,
                                 hipStream_t st) {
-    if (const int nl = l > 0 ? fused_layers(m, l, T) : 0)
-        return launch_fused<FP8>(m, member, l, nl, (const uint16_t*)x_in, (uint16_t*)x_out, skip, nb, T, nullptr, st);
-    LayerArgsLP a = lp_args<FP8>(m, member, l);
+    if (const int nl = l > 0 ? fused_layers(m, l, fb.T) : 0)
+        return launch_fused<FP8>(m, fb.member, l, nl, (const uint16_t*)x_in, (uint16_t*)x_out, skip, fb.nb, fb.T, &fb, st);
+    LayerArgsLP a = lp_args<FP8>(m, fb.member, l);
     a.x_in = (const uint16_t*)x_in;
     a.x_out = (uint16_t*)x_out;
     a.skip = skip;
     a.pre_out = nullptr;
-    a.T = T;
-    return launch_lp<FP8, false, false, false>(a, nb, lp_tiling(m, FP8), st);
+    a.T = fb.T;
+    a.win_rows = fb.rows;
+    return launch_lp<FP8, false, false, false>(a, fb.nb, lp_tiling(m, FP8), st);
 }
 // Layers of the launch that starts at layer l, for the window length of the last forward.
 int layers_per_launch_lp(const gwd_model* m, int l) {
-    const int nl = fused_layers(m, l, m->last_T);
+    const int nl = fused_layers(m, l, m->last.T);
     return nl ? nl : 1;
 }
-hipError_t layer_production_bf16(gwd_model* m, int member, int l, void* xi, void* xo, float* sk, int nb, int T,
-                                 hipStream_t st) {
-    return production_lp<false>(m, member, l, xi, xo, sk, nb, T, st);
+hipError_t layer_production_bf16(gwd_model* m, int l, void* xi, void* xo, float* sk, const FwdBatch& fb, hipStream_t st) {
+    return production_lp<false>(m, l, xi, xo, sk, fb, st);
 }
-hipError_t layer_production_fp8(gwd_model* m, int member, int l, void* xi, void* xo, float* sk, int nb, int T,
-                                hipStream_t st) {
-    return production_lp<true>(m, member, l, xi, xo, sk, nb, T, st);
+hipError_t layer_production_fp8(gwd_model* m, int l, void* xi, void* xo, float* sk, const FwdBatch& fb, hipStream_t st) {
+    return production_lp<true>(m, l, xi, xo, sk, fb, st);
 }
 
 hipError_t wavenet_layers_bf16(gwd_model* m, const FwdBatch& fb, float* x_a, float* x_b, float* skip, hipStream_t st) {

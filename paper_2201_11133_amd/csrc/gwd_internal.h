@@ -100,7 +100,12 @@ struct gwd_model {
     std::vector<void*> canon;                  // device copy of each member's canonical blob (fp32; fp64 for GWD_FP64)
     int32_t batch_windows;                     // windows per layer-kernel batch
     bool merge_windows = true;                 // stitched forwards on merged windows (gwd_set_window_merging)
-    int32_t last_nb = 0, last_T = 0;           // batch shape of the last gwd_forward (workspace contents)
+    struct LastBatch {                         // first batch of the last gwd_forward (workspace contents)
+        int32_t nb = 0, T = 0, n_group = 1;    // windows (0: none), their rows, members per launch
+        int64_t act_stride = 0;
+        const int32_t* rows = nullptr;         // FwdBatch::rows, and the host's copy for its windows
+        std::vector<int32_t> h_rows;
+    } last;
     int64_t ws_tab_bytes = 0;                  // bytes reserved for the stream table at the workspace start
     std::vector<int64_t> host_firsts;          // host copy of FwdBatch::firsts for the current request
     std::vector<int32_t> host_rows;            // host copy of FwdBatch::rows for the current request (empty: none)
@@ -192,8 +197,8 @@ hipError_t launch_fused_recompute(gwd_model* m, int member, int l, int nl, const
 // Layers covered by the launch that starts at layer l (3, 4 or 6 for a fused launch, else 1).
 int layers_per_launch(const gwd_model* m, int l);
 // One production launch of a middle layer on the workspace buffers (timing support).
-hipError_t launch_layer_production(gwd_model* m, int member, int layer, void* x_in, void* x_out, float* skip, int nb,
-                                   int T, hipStream_t st);
+hipError_t launch_layer_production(gwd_model* m, int layer, void* x_in, void* x_out, float* skip, const FwdBatch& fb,
+                                   hipStream_t st);
 
 // Forward sequencing shared by gwd_forward and the captured plans (api.cpp).
 gwd_status check_forward(const gwd_model* m, const gwd_stream* streams, int32_t n_streams, int32_t window,

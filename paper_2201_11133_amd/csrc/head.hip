@@ -242,16 +242,16 @@ hipError_t launch_stamp(unsigned long long* slot, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t layer_production_f32(gwd_model*, int, int, void*, void*, float*, int, int, hipStream_t);
-hipError_t layer_production_bf16(gwd_model*, int, int, void*, void*, float*, int, int, hipStream_t);
-hipError_t layer_production_fp8(gwd_model*, int, int, void*, void*, float*, int, int, hipStream_t);
+hipError_t layer_production_f32(gwd_model*, int, void*, void*, float*, const FwdBatch&, hipStream_t);
+hipError_t layer_production_bf16(gwd_model*, int, void*, void*, float*, const FwdBatch&, hipStream_t);
+hipError_t layer_production_fp8(gwd_model*, int, void*, void*, float*, const FwdBatch&, hipStream_t);
 
-hipError_t launch_layer_production(gwd_model* m, int member, int layer, void* x_in, void* x_out, float* skip, int nb,
-                                   int T, hipStream_t st) {
+hipError_t launch_layer_production(gwd_model* m, int layer, void* x_in, void* x_out, float* skip, const FwdBatch& fb,
+                                   hipStream_t st) {
     switch (m->prec) {
-        case GWD_FP32: return layer_production_f32(m, member, layer, x_in, x_out, skip, nb, T, st);
-        case GWD_BF16: return layer_production_bf16(m, member, layer, x_in, x_out, skip, nb, T, st);
-        default: return layer_production_fp8(m, member, layer, x_in, x_out, skip, nb, T, st);
+        case GWD_FP32: return layer_production_f32(m, layer, x_in, x_out, skip, fb, st);
+        case GWD_BF16: return layer_production_bf16(m, layer, x_in, x_out, skip, fb, st);
+        default: return layer_production_fp8(m, layer, x_in, x_out, skip, fb, st);
     }
 }
 

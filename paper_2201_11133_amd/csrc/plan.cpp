@@ -14,6 +14,7 @@
 #include <algorithm>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "gwd_internal.h"
@@ -68,7 +69,7 @@ gwd_status gwd_plan_create(gwd_model* m, const gwd_stream* streams, int32_t n_st
     // capture into a workspace of the plan's own: swap it into the model for the capture, then back
     const Workspace saved_ws = m->ws;
     const int64_t saved_tab = m->ws_tab_bytes;
-    const int32_t saved_nb = m->last_nb, saved_T = m->last_T;
+    gwd_model::LastBatch saved_last = m->last;
     m->ws = Workspace{};
     m->ws_tab_bytes = 0;
     auto restore = [&](gwd_plan* p) {
@@ -76,8 +77,7 @@ gwd_status gwd_plan_create(gwd_model* m, const gwd_stream* streams, int32_t n_st
         else if (m->ws.base) (void)hipFree(m->ws.base);
         m->ws = saved_ws;
         m->ws_tab_bytes = saved_tab;
-        m->last_nb = saved_nb;
-        m->last_T = saved_T;
+        m->last = std::move(saved_last);
     };
     gwd_status s = forward_prepare(m, streams, n_streams, window, stride, out_mode, out, out_capacity_floats, nullptr,
                                    true, fb, total_win, nb_max, &nwin);
