@@ -410,7 +410,11 @@ gwd_status gwd_adam_step(gwd_model* model, int32_t member, float* master, const 
  * gwd_plan_completion_us (after a launch; synchronises the device) gives, per
  * stream, the time from the plan's start to the end of the batch holding the
  * stream's last window (persistent forward: to the end of the stream's last
- * window to finish), and the total, in microseconds. */
+ * window to finish), and the total, in microseconds. A batch holds up to
+ * batch_windows x window rows (gwd_set_tiling), which with merged windows
+ * (gwd_set_window_merging) are that many samples of strain: streams of one
+ * batch complete together, a request of a few minutes in one or two batches.
+ * A smaller batch_windows, or merging off, gives finer times. */
 typedef struct gwd_plan gwd_plan;
 gwd_status gwd_plan_create(gwd_model* model, const gwd_stream* streams, int32_t n_streams, int32_t window,
                            int32_t stride, int32_t out_mode, float* out, int64_t out_capacity_floats,
@@ -474,10 +478,13 @@ gwd_status gwd_set_persistent(gwd_model* model, int32_t on);
  * only, and compute no row twice that the scores do not need twice. The
  * scores are bit for bit those of the request's own windows, and the
  * workspace stays within that of one batch of them (batch_windows x window
- * rows; a small request may take several members' rows of it at once). on = 0 runs every row of every window of the request, as an engine that maps
- * windows to windows does ("Optimization with TensorRT"). out_mode 2, the
- * small member and the persistent forward always do. GWD_ERR_ARG unless on is
- * 0 or 1. */
+ * rows; a small request may take several members' rows of it at once).
+ * Requests whose own windows cost less (short streams beside a long one) keep
+ * them. A plan on merged windows has fewer batches, so the completion times of
+ * its streams are coarser (gwd_plan_completion_us). on = 0 runs every row of
+ * every window of the request, as an engine that maps windows to windows does
+ * ("Optimization with TensorRT"). out_mode 2, the small member and the
+ * persistent forward always do. GWD_ERR_ARG unless on is 0 or 1. */
 gwd_status gwd_set_window_merging(gwd_model* model, int32_t on);
 
 /* Autotuner (the engine's kernel choice by profiling, "Optimization with
