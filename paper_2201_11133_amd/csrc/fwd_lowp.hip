@@ -22,6 +22,7 @@
 //   64 x 8 (RB 1, 4 waves/SIMD, two passes)
 //   128 x 4 (RB 4, 2 waves/SIMD, one pass: each operand fragment feeds both column blocks)
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "gwd_internal.h"
@@ -342,7 +343,7 @@ void layer_lp_kernel(LayerArgsLP p) {
                     po[n] = to_bf16_bits(vf);
                     po[kC + n] = to_bf16_bits(vg);
                 }
-                const float gv = gate_fast(vf, vg);
+                const float gv = gate_lowp<true>(vf, vg);
                 if (FP8) {  // rows m (i even) and m + 1 (i odd) converted together
                     if (i & 1) {
                         const uint32_t c2 = e4m3_pair_in_range(gprev, gv);
@@ -582,6 +583,13 @@ __device__ inline void store_col16(float* b, const floatx16& v) {
 typedef float float2v __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t pack_bf16x2(float a, float b) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((float2v){a, b}, bf16x2v));
+}
+
+// The gate of four channels i .. i + 3 of a row block's accumulators, packed (gate_lowp).
+template <bool SAFE>
+__device__ inline uint2 gate4_bf16(const floatx16& f, const floatx16& g, int i) {
+    return make_uint2(pack_bf16x2(gate_lowp<SAFE>(f[i], g[i]), gate_lowp<SAFE>(f[i + 1], g[i + 1])),
+                      pack_bf16x2(gate_lowp<SAFE>(f[i + 2], g[i + 2]), gate_lowp<SAFE>(f[i + 3], g[i + 3])));
 }
 
 // x + v for four bf16 channels held in w, rounded back to bf16.

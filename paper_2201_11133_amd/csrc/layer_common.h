@@ -12,15 +12,20 @@ __device__ inline float gate_f32(float af, float ag) { return tanhf(af) * sigmoi
 // The same gate for the reduced-precision paths, whose result is rounded to bf16 / E4M3 right away:
 // with E = e^(-2|a|) and E_b = e^-b, tanh(a) sigmoid(b) = sign(a) (1 - E) / ((1 + E)(1 + E_b)), from
 // two hardware exp2 and one reciprocal (a few ulp in fp32, far below the bf16 rounding step). E lies
-// in [2^-126, 1] for every a, so nothing overflows on the tanh side; a denominator that overflows gives
-// 0 where the true value is below 1e-30; a NaN from a or b propagates. E stops at 2^-126 because 0 times
-// an infinite 1 + E_b is NaN (|a| > 43 with b < -88, a loud glitch); 1 - E and E (1 + E_b) + (1 + E_b)
-// round alike for 2^-126 and 0, so no other result depends on it (one vector instruction more per gate: 512
-// windows in BF16 15.25 -> 15.43 ms, ragged FP8 streams 2.26 -> 2.29 ms).
-__device__ inline float gate_fast(float af, float ag) {
+// in [0, 1] for every a, so nothing overflows on the tanh side; a denominator that overflows gives 0
+// where the true value is below 1e-30; a NaN from a or b propagates. Where E has underflowed and 1 + E_b
+// overflowed (|a| > 43 with b < -88, a loud glitch) their product is NaN, not 0: with SAFE, E stops at 2^-126
+// instead. 1 - E and E (1 + E_b) + (1 + E_b) round alike for 2^-126 and 0, so nothing else depends on it.
+// The fused kernels, bound by vector instructions, take the short form and repeat a lane's outputs where one came
+// out as NaN: the bit of 2 in the exponents of the packed outputs (all below 2) tells. 512 windows in BF16
+// 15.36 ms without a check, 15.42 with it, 15.54 with the limit in every gate; ragged FP8 streams 2.28,
+// 2.28, 2.32 ms.
+template <bool SAFE>
+__device__ inline float gate_lowp(float af, float ag) {
     const float kLog2e = 1.4426950408889634f;
-    // e^(-2|a|); the maximum keeps a NaN (fmaxf would drop it)
-    const float ea = __builtin_amdgcn_exp2f(__builtin_elementwise_maximum(-2.f * kLog2e * fabsf(af), -126.f));
+    float xa = -2.f * kLog2e * fabsf(af);
+    if (SAFE) xa = __builtin_elementwise_maximum(xa, -126.f);   // (it keeps a NaN; fmaxf would drop it)
+    const float ea = __builtin_amdgcn_exp2f(xa);                // e^(-2|a|)
     const float eb = __builtin_amdgcn_exp2f(-kLog2e * ag);
     const float ob = 1.f + eb;
     return copysignf((1.f - ea) * __builtin_amdgcn_rcpf(fmaf(ea, ob, ob)), af);
