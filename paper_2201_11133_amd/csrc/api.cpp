@@ -188,7 +188,9 @@ gwd_status check_forward(const gwd_model* m, const gwd_stream* streams, int32_t 
 // own windows. Windows 4096 / 256, four members in BF16: 8 s of strain 15.1 -> 1.94 ms (1.20 ms with the
 // members in one launch), 256 s 459 -> 31.3 ms; one FP32 member, 16 s: 84.6 -> 6.03 ms.
 constexpr int64_t kRowBytes = 3 * kC * 4;      // workspace per row: x ping-pong and skip
-constexpr int64_t kMostRows = 1 << 22;         // rows that a merged window or a group of members may take together
+// Rows that a merged window or a group of members may take together: 6.4 GB of workspace. (900 s in windows of
+// 65,536 or 262,144: 110.3 to 111.5 ms with 2^21, 2^22 and 2^23.)
+constexpr int64_t kMostRows = 1 << 22;
 
 // Bytes that the activations may take: 60 % of the device memory free now, with what the model holds.
 static int64_t allowed_bytes(const gwd_model* m) {
@@ -221,7 +223,9 @@ static double request_cost(const gwd_model* m, int64_t rows, int64_t total_win, 
 // Of the longest windows allowed and their halves down to the request's own length, the cheapest; false
 // if the request's own windows cost less. (A window reserves the longest one's rows: with windows as long as
 // the longest stream, 64 s beside 4,000 streams of 1 s ran in 501 batches of 8 windows, four members in BF16
-// 5,504 ms; 524 ms so, 606 ms in the request's own windows.)
+// 5,504 ms; 524 ms so, 606 ms in the request's own windows.) Of several streams no window is longer than an
+// eighth of a batch: with up to a whole one, streams of 200, 100 and 50 s took 59.9 ms, not 43.7, three of 100 s
+// 38.5, not 37.4; two of 400 s 97.8, not 99.8.
 static bool merged_windows(const gwd_model* m, const gwd_stream* streams, int n_streams, int64_t total_win, int& window,
                            int& stride) {
     const int64_t H = (rf_of(&m->arch) - 1 + 127) / 128 * 128;   // overlap: whole 128-row tiles
