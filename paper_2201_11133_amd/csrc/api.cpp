@@ -274,6 +274,7 @@ gwd_status ensure_workspace(gwd_model* m, int64_t bytes, hipStream_t st) {
         (void)hipFree(m->ws.base);
         m->ws.base = nullptr;
         m->ws.bytes = 0;
+        m->last.nb = 0;
     }
     e = hipMalloc(&m->ws.base, bytes);
     if (e != hipSuccess) return hip_fail(e, "hipMalloc(workspace)");
