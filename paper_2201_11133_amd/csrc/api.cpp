@@ -27,6 +27,7 @@ void set_error(const char* fmt, ...) {
 
 gwd_status hip_fail(hipError_t e, const char* what) {
     set_error("%s failed: %s", what, hipGetErrorString(e));
+    (void)hipGetLastError();   // reported here, and not by the next call's check of its launches once more
     return GWD_ERR_HIP;
 }
 
